@@ -1,0 +1,59 @@
+"""The fp32 read on the fp32 matrix instructions against the float64 oracle:
+tile and width edges, the exact recomputation, and NaN confined to its rows.
+
+Tolerance 1e-4 (max abs), the fp32 budget; the kernel's own rounding is about
+2^-22 of an output at beta >= 0.25.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_07160_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-4
+
+
+def read(fem, *x):
+    print("[case]", [tuple(t.shape) for t in x], flush=True)
+    out = fem.fem_softmax_fwd(*(t.cuda() for t in x))
+    torch.cuda.synchronize()
+    return out.cpu().double().numpy()
+
+
+def ref(*x):
+    return oracle.fem_softmax(*(t.double().numpy() for t in x))
+
+
+# 32-row blocks and 32-key tiles over four waves: one wave only, a full and a
+# ragged last tile, a second tile per wave; widths: each padded width, a
+# multiple of four and a ragged one below it
+@pytest.mark.parametrize("T", [1, 31, 32, 33, 127, 129, 161])
+@pytest.mark.parametrize("d", [1, 7, 32, 36, 64, 100, 128, 130, 252, 256])
+def test_edges(fem, T, d):
+    x = inputs.draw(9000 + 300 * T + d, 1, 2, T, d, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+    assert np.abs(read(fem, *x) - ref(*x)).max() <= TOL
+
+
+@pytest.mark.parametrize("T,d", [(70, 32), (300, 64), (200, 100), (130, 256)])
+def test_late_maximum_is_recomputed(fem, T, d):
+    """Values far below the last key's: every earlier row's weighted mean of E
+    underflows against the shared column maximum."""
+    q, k, v, _ = inputs.draw(9500 + d, 1, 2, T, d, dtype="f32")
+    v = -5.0 + 0.1 * v
+    v[:, :, -1] = 5.0
+    b = torch.full((2, d), 16.0)
+    assert np.abs(read(fem, q, k, v, b) - ref(q, k, v, b)).max() <= TOL
+
+
+def test_nan_value_reaches_its_rows_only(fem):
+    q, k, v, b = inputs.draw(9600, 1, 1, 100, 64, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+    want = ref(q, k, v, b)
+    v[0, 0, 70, 5] = float("nan")
+    got = read(fem, q, k, v, b)
+    assert np.isnan(got[0, 0, 70:, 5]).all()
+    got[0, 0, 70:, 5] = want[0, 0, 70:, 5]
+    assert np.abs(got - want).max() <= TOL
