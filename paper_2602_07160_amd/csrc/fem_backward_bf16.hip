@@ -580,8 +580,8 @@ __global__ __launch_bounds__(kThreads) void bwd_q_kernel(
 //          v dV terms of dbeta;
 //   dbeta: per (h, j), the partial sums in double precision.
 // The streamed side of a pass (K, Y in the q pass; Q, W U' in the kv pass)
-// goes global -> LDS by direct loads into a double buffer, one tile pair
-// ahead, so the loads cost no registers and no waiting; the transposed
+// goes global -> LDS by direct loads into three buffers, one tile pair
+// ahead, so the loads cost no registers; the transposed
 // operands (K^T, Y^T; Q^T, (W U')^T) are read from the same row-major tiles
 // by transposing LDS reads (ds_read_b64_tr_b16).
 
@@ -590,37 +590,11 @@ __device__ __forceinline__ void split_bf16(float x, bf16& hi, bf16& lo) {
   lo = (bf16)(x - (float)hi);
 }
 
-// p and dS of a 32 x 32 block as MFMA B operands (k = the accumulator's
-// rows): hi / lo parts of p and bf16 dS, two values per conversion.
-// pc(r) gives accumulator row r's p and row constant c_r; dS = p (dP + c_r).
-template <class PC>
-__device__ __forceinline__ void pack_p_ds(PC&& pc, const f32x16& dp, bf16x8 (&ph)[2],
-                                          bf16x8 (&pl)[2], bf16x8 (&ds)[2]) {
-  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
-  u32x4 h[2], l[2], d[2];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const f32x2 x = pc(2 * k), y = pc(2 * k + 1);  // (p, c)
-    const float a = x[0], b = y[0];
-    const unsigned hu = __builtin_bit_cast(unsigned, to_bf16x2(a, b));
-    const float ha = __uint_as_float(hu << 16), hb = __uint_as_float(hu & 0xffff0000u);
-    h[k >> 2][k & 3] = hu;
-    l[k >> 2][k & 3] = __builtin_bit_cast(unsigned, to_bf16x2(a - ha, b - hb));
-    d[k >> 2][k & 3] = __builtin_bit_cast(
-        unsigned, to_bf16x2(a * (dp[2 * k] + x[1]), b * (dp[2 * k + 1] + y[1])));
-  }
-#pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    ph[g] = __builtin_bit_cast(bf16x8, h[g]);
-    pl[g] = __builtin_bit_cast(bf16x8, l[g]);
-    ds[g] = __builtin_bit_cast(bf16x8, d[g]);
-  }
-}
-
 __device__ __forceinline__ f32x16 mfma(const bf16x8& a, const bf16x8& b, const f32x16& c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
+constexpr int kFastWaves = 8;    // waves of the matrix-core passes
 constexpr float kRange = 110.f;  // largest bl (max v - min v) of a channel
 constexpr float kSplit = 4.f;    // largest bl (max v - min v) of a split channel
 constexpr float kGuardU = 120.f; // largest log2 U of a row
@@ -635,23 +609,258 @@ __device__ __forceinline__ int xcd_order(int b, int nblk) {
 }
 
 
-// Direct global -> LDS copy of rows [0, 64) of a row-major [., D] bf16 source
-// into a swizzled tile; rows past lim re-read row lim (their keys or queries
-// are masked).  Wave w fills the 1 KiB blocks w, w + 4, ...: lane l of block
-// b fills slot 64 b + l, i.e. row (64 b + l) / (D / 8), chunk position
-// (64 b + l) % (D / 8), from the chunk that position holds.
+// Direct global -> LDS copy of the 64 rows that a buffer resource covers (a
+// row-major [., D] bf16 source; rows past its end load as zeros, their keys or
+// queries are masked) into a swizzled tile.  Wave w fills the 1 KiB blocks w, w + 8, ...: lane l of
+// block b fills slot 64 b + l, i.e. row (64 b + l) / (D / 8), chunk position
+// (64 b + l) % (D / 8), from the chunk that position holds (lane offset
+// `off` for block w; 8 blocks on is a whole number of 32-row groups on, at the
+// same swizzle).
 template <int D>
-__device__ __forceinline__ void load_swz(const bf16* __restrict__ src, bf16* dst, int lim) {
+__device__ __forceinline__ unsigned swz_lane(int wave, int lane) {
   constexpr int CPR = D / 8;
-  static_assert(CPR % 4 == 0, "whole blocks per wave");
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const char* s8 = reinterpret_cast<const char*>(src);
+  const int s = wave * 64 + lane, row = s / CPR, pos = s % CPR;
+  return (unsigned)(row * D * 2 + ((pos ^ swz<D>(row)) << 4));
+}
+// Loads of one wave for a tile of three arrays, numbered 0 .. kLoads<D> - 1.
+template <int D>
+constexpr int kBlocksPerWave = (D / 8 + kFastWaves - 1) / kFastWaves;
+template <int D>
+constexpr int kLoads = 3 * kBlocksPerWave<D>;
+template <int D>
+__device__ __forceinline__ void load_swz(rsrc_t r, unsigned lds, int wave_s, unsigned off, int u) {
+  constexpr int BLOCKS = D / 8;
+  static_assert(BLOCKS <= kFastWaves || (kFastWaves * 64 / BLOCKS) % 32 == 0, "same swizzle");
+  const int blk = wave_s + kFastWaves * u;
+  if (BLOCKS % kFastWaves == 0 || blk < BLOCKS)
+    dma16b(r, off + (unsigned)(u * kFastWaves * 1024), lds + (unsigned)blk * 1024u);
+}
+
+// Operand fragments of the swizzled tiles of a buffer, by LDS byte address.
+// With the tile at a multiple of 256 bytes the swizzled chunk sits in address
+// bits of its own, so every fragment of a lane is (base ^ constant) +
+// constant: one register per tile and one xor per distinct chunk, the three
+// arrays of a buffer and the 16-row steps through the offset field.
+__device__ __forceinline__ bf16x8 lds_read16(unsigned a) {
+  typedef __attribute__((address_space(3))) const bf16x8 lds_t;
+  return *(lds_t*)(uintptr_t)a;
+}
+// row-major: 8 bf16 of row `row`, chunk 2 ks + hl
+template <int D>
+__device__ __forceinline__ unsigned rows_base(int row, int hl) {
+  return (unsigned)(row * D * 2 + ((hl ^ swz<D>(row)) << 4));
+}
+__device__ __forceinline__ bf16x8 rows_at(unsigned base, int ks, int array_bytes) {
+  return lds_read16((base ^ (unsigned)(ks << 5)) + (unsigned)array_bytes);
+}
+// transposed (frag_tr): columns 32 b .., positions r0 + 16 k2 .. (r0 a
+// multiple of 32).  The second read's rows are 8 further on.
+template <int D>
+__device__ __forceinline__ unsigned tr_base(int r0, int lane) {
+  const int g = lane >> 4, i = lane & 15, q = i & 3;
+  const int row = r0 + 4 * (g >> 1) + (i >> 2);
+  return (unsigned)(row * D * 2 + (((2 * (g & 1) + (q >> 1)) ^ swz<D>(row)) << 4) + (q & 1) * 8);
+}
+template <int D>
+__device__ __forceinline__ bf16x8 tr_at(unsigned base, int b, int k2, int array_bytes) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const unsigned a = base ^ (unsigned)(b << 6), imm = (unsigned)(array_bytes + k2 * 16 * D * 2);
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(uintptr_t)(a + imm));
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (lds_s16x4*)(uintptr_t)((a ^ 32u) + imm + 8 * D * 2));
+  const s16x8 x = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(bf16x8, x);
+}
+
+// ---- one tile pair of a role, as a fixed sequence of slots ------------------
+//
+// A slot issues one MFMA, the LDS read of the operand fragment kRing steps
+// ahead and a slice of vector work; a scheduling barrier after every slot
+// keeps this order.  Left to itself the compiler kept one fragment in flight
+// and waited for it before every product (LDS latency, ~100 cycles, against
+// 32 of issue).
+constexpr int kRing = 4;
+// The next tile's direct loads go out one every kLoadEvery slots: issued
+// together after the barrier they filled the memory pipeline and held half of
+// the waves for ~1800 cycles of a tile pair (4950 cycles, 3800 spread out).
+constexpr int kLoadEvery = 3;
+template <int D, class Load>
+__device__ __forceinline__ void load_slot(int slot, Load&& load) {
+  if (slot % kLoadEvery == 0 && slot / kLoadEvery < kLoads<D>) load(slot / kLoadEvery);
+}
+
+// p or dS of accumulator rows 2k, 2k + 1 as element pair k of MFMA B operands
+// (k = the accumulator's rows).
+__device__ __forceinline__ void put_pair(bf16x8 (&x)[2], int k, bf16x2 v) {
+  x[k >> 2][2 * (k & 3)] = v[0];
+  x[k >> 2][2 * (k & 3) + 1] = v[1];
+}
+
+// The dQ / dK role.  rb, tb: LDS bases of this tile's row-major and the tile
+// before's transposed fragments; f0 / wf: the loop-invariant operands of S and
+// dP.  On entry pv and dp hold p and dP of the tile before (PREV), on exit
+// this one's.  arg(r, s): log2 p of accumulator row r (masked); cst(r): the
+// row constant of row r of the tile before.
+//   S (NKS products)       || dS = p (dP + c) of the tile before
+//   transposed (2 NB)      || the exponents of p
+//   dP (3 NKS)             || p
+template <int D, bool PREV, class Arg, class Cst, class Load>
+__device__ __forceinline__ void step_ds(unsigned rb, unsigned tb, const bf16x8 (&f0)[D / 16],
+                                        const bf16x8 (&wf)[D / 16][2], f32x16 (&acc)[D / 32],
+                                        f32x16& pv, f32x16& dp, Arg&& arg, Cst&& cst,
+                                        Load&& load) {
+  constexpr int NKS = D / 16, NT = PREV ? D / 16 : 0, AB = kTile * D * 2;
+  constexpr int NF = NKS + NT + 2 * NKS;
+  const auto frag = [&](int f) __attribute__((always_inline)) {
+    if (f < NKS) return rows_at(rb, f, 0);
+    if (f < NKS + NT) return tr_at<D>(tb, (f - NKS) >> 1, (f - NKS) & 1, 0);
+    const int y = f - NKS - NT;
+    return rows_at(rb, y >> 1, AB * (1 + (y & 1)));
+  };
+  bf16x8 ring[kRing], ds[2];
 #pragma unroll
-  for (int u = 0; u < CPR / 4; ++u) {
-    const int blk = wave + 4 * u;
-    const int s = blk * 64 + lane, row = s / CPR, pos = s % CPR;
-    const unsigned off = (unsigned)(min(row, lim) * D * 2 + ((pos ^ swz<D>(row)) << 4));
-    dma16(s8 + off, dst + blk * 512);
+  for (int f = 0; f < kRing; ++f) ring[f] = frag(f);
+  f32x16 s = {};
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int st = 0; st < NKS; ++st) {
+    s = mfma(ring[st % kRing], f0[st], s);
+    ring[st % kRing] = frag(st + kRing);
+    load_slot<D>(st, load);
+    if (PREV) {
+#pragma unroll
+      for (int k = st * 8 / NKS; k < (st + 1) * 8 / NKS; ++k)
+        put_pair(ds, k, to_bf16x2(pv[2 * k] * (dp[2 * k] + cst(2 * k)),
+                                  pv[2 * k + 1] * (dp[2 * k + 1] + cst(2 * k + 1))));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int g = 0; g < NT; ++g) {
+    const int f = NKS + g;
+    acc[g >> 1] = mfma(ring[f % kRing], ds[g & 1], acc[g >> 1]);
+    if (f + kRing < NF) ring[f % kRing] = frag(f + kRing);
+    load_slot<D>(NKS + g, load);
+    // (the first slot leaves the last product of S time to finish)
+    if (g > 0) {
+#pragma unroll
+      for (int r = (g - 1) * 16 / (NT - 1); r < g * 16 / (NT - 1); ++r) pv[r] = arg(r, s[r]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  dp = f32x16{};
+#pragma unroll
+  for (int u = 0; u < 3 * NKS; ++u) {
+    const int ks = u / 3, j = u % 3, f = NKS + NT + 2 * ks + (j == 2);
+    dp = mfma(ring[f % kRing], wf[ks][j == 1], dp);
+    if (j > 0 && f + kRing < NF) ring[f % kRing] = frag(f + kRing);
+    load_slot<D>(NKS + NT + u, load);
+    // p of 16 / (3 NKS - 2) rows a slot, two slots in
+    const int lo = (u - 1) * 16 / (3 * NKS - 2), hi = u * 16 / (3 * NKS - 2);
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+      if (u > 0 && r >= lo && r < hi) pv[r] = exp2_hw(PREV ? pv[r] : arg(r, s[r]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+// The last tile's share: dS and its transposed products.
+template <int D, class Cst>
+__device__ __forceinline__ void finish_ds(unsigned tb, f32x16 (&acc)[D / 32], const f32x16& pv,
+                                          const f32x16& dp, Cst&& cst) {
+  bf16x8 ds[2];
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    put_pair(ds, k, to_bf16x2(pv[2 * k] * (dp[2 * k] + cst(2 * k)),
+                              pv[2 * k + 1] * (dp[2 * k + 1] + cst(2 * k + 1))));
+#pragma unroll
+  for (int g = 0; g < D / 16; ++g)
+    acc[g >> 1] = mfma(tr_at<D>(tb, g >> 1, g & 1, 0), ds[g & 1], acc[g >> 1]);
+}
+
+// The SA / dV role.  On entry ph, pl hold the tile before's p (PREV), on exit
+// this one's; seen(p) is called with every p.
+//   S (NKS products), then transposed (6 NB)  || p, rounded to hi and lo parts
+template <int D, bool PREV, class Arg, class Seen, class Load>
+__device__ __forceinline__ void step_p(unsigned rb, unsigned tb, const bf16x8 (&f0)[D / 16],
+                                       f32x16 (&acc)[D / 32], bf16x8 (&ph)[2], bf16x8 (&pl)[2],
+                                       Arg&& arg, Seen&& seen, Load&& load) {
+  constexpr int NKS = D / 16, NT = PREV ? 2 * (D / 16) : 0, AB = kTile * D * 2;
+  constexpr int NF = NKS + NT;
+  const auto frag = [&](int f) __attribute__((always_inline)) {
+    if (f < NKS) return rows_at(rb, f, 0);
+    const int g = (f - NKS) >> 1;
+    return tr_at<D>(tb, g >> 1, g & 1, AB * (1 + (f & 1)));
+  };
+  bf16x8 ring[kRing];
+#pragma unroll
+  for (int f = 0; f < kRing; ++f)
+    if (f < NF) ring[f] = frag(f);
+  f32x16 s = {};
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int st = 0; st < NKS; ++st) {
+    s = mfma(ring[st % kRing], f0[st], s);
+    if (st + kRing < NF) ring[st % kRing] = frag(st + kRing);
+    load_slot<D>(st, load);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  bf16x8 nh[2], nl[2];
+  // entry pair k in three stages: the exponents, 2^, and the parts
+  const auto stage = [&](int v) __attribute__((always_inline)) {
+    const int k = v / 3;
+    if (v % 3 == 0) {
+      s[2 * k] = arg(2 * k, s[2 * k]);
+      s[2 * k + 1] = arg(2 * k + 1, s[2 * k + 1]);
+    } else if (v % 3 == 1) {
+      s[2 * k] = exp2_hw(s[2 * k]);
+      s[2 * k + 1] = exp2_hw(s[2 * k + 1]);
+    } else {
+      const float a = s[2 * k], b = s[2 * k + 1];
+      seen(a);
+      seen(b);
+      const bf16x2 h = to_bf16x2(a, b);
+      const unsigned hu = __builtin_bit_cast(unsigned, h);
+      put_pair(nh, k, h);
+      put_pair(nl, k, to_bf16x2(a - __uint_as_float(hu << 16),
+                                b - __uint_as_float(hu & 0xffff0000u)));
+    }
+  };
+  if (!PREV) {
+#pragma unroll
+    for (int x = NKS; x < kLoadEvery * kLoads<D>; ++x) load_slot<D>(x, load);
+#pragma unroll
+    for (int v = 0; v < 24; ++v) stage(v);
+  } else {
+    constexpr int NU = 3 * (NT / 2);  // products: fh ph, fh pl, fl ph
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int g = u / 3, j = u % 3, f = NKS + 2 * g + (j == 2);
+      acc[g >> 1] = mfma(ring[f % kRing], j == 1 ? pl[g & 1] : ph[g & 1], acc[g >> 1]);
+      if (j > 0 && f + kRing < NF) ring[f % kRing] = frag(f + kRing);
+      load_slot<D>(NKS + u, load);
+#pragma unroll
+      for (int v = u * 24 / NU; v < (u + 1) * 24 / NU; ++v) stage(v);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    ph[g] = nh[g];
+    pl[g] = nl[g];
+  }
+}
+template <int D>
+__device__ __forceinline__ void finish_p(unsigned tb, f32x16 (&acc)[D / 32], const bf16x8 (&ph)[2],
+                                         const bf16x8 (&pl)[2]) {
+  constexpr int AB = kTile * D * 2;
+#pragma unroll
+  for (int g = 0; g < D / 16; ++g) {
+    const int b = g >> 1, k2 = g & 1;
+    const bf16x8 fh = tr_at<D>(tb, b, k2, AB), fl = tr_at<D>(tb, b, k2, 2 * AB);
+    acc[b] = mfma(fh, ph[k2], acc[b]);
+    acc[b] = mfma(fh, pl[k2], acc[b]);
+    acc[b] = mfma(fl, ph[k2], acc[b]);
   }
 }
 
@@ -821,10 +1030,20 @@ __global__ __launch_bounds__(kThreads) void bwd_prepk_kernel(
   if (bad) flag[0] = 1;
 }
 
-// q kernel, matrix-core form.  Wave (kh = w >> 1, qh = w & 1) owns the
-// S^T block (keys kh*32.., queries qh*32..) of each tile pair; its query
-// rows' operands (Q and W U hi / lo as MFMA B fragments), row constant and
-// log-normaliser stay in registers.
+// q kernel, matrix-core form.  Eight waves, two a SIMD: wave w and wave w + 4
+// work on the same S^T block (keys kh*32.., queries qh*32.., kh = w >> 1 & 1,
+// qh = w & 1) of each tile pair in two roles, which both form S^T and p:
+//   dq (w < 4): dP^T = Y (W U)^T, dS, dQ^T += K^T dS^T; its query rows' Q and
+//               W U hi / lo stay in registers as MFMA B fragments;
+//   sa (w >= 4): SA^T += Y^T P^T and the row sums P.
+// One wave doing both kept 224 registers of operands and accumulators, so a
+// SIMD held one wave and its products waited for its own vector work: 64
+// products (2048 cycles) in ~5300 cycles per tile pair at d = 128.  Split,
+// the pair issues 72 (S^T twice) in ~3800: one role's products run under the
+// other's vector work, and each fits in 256 registers.  Both passes together
+// at B4 H4 T2048 d128 223 us before, 166 now (the whole call 304 and 248); at
+// B8 H16 T4096 d128, where the products' power draw lowers the clock from 2.3
+// to 1.8 GHz, 5.3 ms and 4.7 (5.97 and 5.40); at d = 64 3.48 and 3.02 a call.
 template <int D>
 struct QFast {
   bf16 key[3][3][kTile * D];  // [buffer][K, Y hi, Y lo], swizzled [key][d or j]
@@ -832,142 +1051,130 @@ struct QFast {
 };
 
 template <int D>
-__global__ __launch_bounds__(kThreads) void bwd_q_fast_kernel(
+__global__ __launch_bounds__(kFastWaves * 64) void bwd_q_fast_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const float* __restrict__ lse,
     const bf16* __restrict__ yh, const bf16* __restrict__ yl, const bf16* __restrict__ wh,
     const bf16* __restrict__ wl, const float* __restrict__ cst, float* __restrict__ dQ,
     float* __restrict__ sap, float* __restrict__ lse_p, int T, int ntile) {
   using C = Bw<D>;
   constexpr int NB = C::NCB;
-  __shared__ __align__(16) QFast<D> sm;
+  __shared__ __align__(256) QFast<D> sm;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, hl = lane >> 5;
   const int lb = xcd_order(blockIdx.x, gridDim.x);
   const int qb = ntile - 1 - lb % ntile, bh = lb / ntile;
   const int q0 = qb * kTile;
   const size_t base = (size_t)bh * T * D;
   const size_t rows0 = (size_t)bh * ntile * kTile;
-  const int kh = wave >> 1, qh = wave & 1;
-  auto fetch = [&](int kb) {
-    const int k0 = kb * kTile;
-    bf16* dst = &sm.key[kb % 3][0][0];
-    load_swz<D>(K + base + (size_t)k0 * D, dst, T - 1 - k0);
-    load_swz<D>(yh + (rows0 + k0) * D, dst + kTile * D, kTile - 1);
-    load_swz<D>(yl + (rows0 + k0) * D, dst + 2 * kTile * D, kTile - 1);
+  const int kh = (wave >> 1) & 1, qh = wave & 1;
+  constexpr int AB = kTile * D * 2;  // bytes of one tile array
+  const unsigned lds0 = lds_addr(&sm.key[0][0][0]);
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const bool role_dq = wave_s < 4;
+  const unsigned loff = swz_lane<D>(wave, lane);
+  const unsigned rbase = rows_base<D>(kh * 32 + n, hl), tbase = tr_base<D>(kh * 32, lane);
+  auto buffer = [&](int kb) { return lds0 + (unsigned)(kb % 3) * (3 * AB); };
+  // load x (of kLoads) of key tile kb
+  auto fetch = [&](int kb, int x) __attribute__((always_inline)) {
+    const int k0 = kb * kTile, a = x / kBlocksPerWave<D>;
+    const rsrc_t r = a == 0 ? buffer_rsrc(K + base + (size_t)k0 * D, (unsigned)min(T - k0, kTile) * D * 2u)
+                            : buffer_rsrc((a == 1 ? yh : yl) + (rows0 + k0) * D, (unsigned)AB);
+    load_swz<D>(r, buffer(kb) + a * AB, wave_s, loff, x % kBlocksPerWave<D>);
   };
-  fetch(0);
+#pragma unroll
+  for (int x = 0; x < kLoads<D>; ++x) fetch(0, x);
 
   const int t = qh * 32 + n;
   // this wave's query rows as MFMA B fragments: Q (for S^T; rows past T
-  // re-read row T - 1, their p is masked) and W U hi / lo (for dP^T, zero
-  // past T), loop-invariant
-  bf16x8 qf[C::NKS], wf[C::NKS][2];
+  // re-read row T - 1, their p is masked), loop-invariant
+  bf16x8 qf[C::NKS];
   {
-    const size_t qr = base + (size_t)min(q0 + t, T - 1) * D, wr = (rows0 + q0 + t) * D;
+    const size_t qr = base + (size_t)min(q0 + t, T - 1) * D;
 #pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
+    for (int ks = 0; ks < C::NKS; ++ks)
       qf[ks] = *reinterpret_cast<const bf16x8*>(Q + qr + ks * 16 + hl * 8);
-      wf[ks][0] = *reinterpret_cast<const bf16x8*>(wh + wr + ks * 16 + hl * 8);
-      wf[ks][1] = *reinterpret_cast<const bf16x8*>(wl + wr + ks * 16 + hl * 8);
-    }
   }
-  const float ct = cst[rows0 + q0 + t];
   const float l2 = q0 + t < T ? lse[(size_t)bh * T + q0 + t] * kLog2e : 0.f;
 #pragma unroll
-  for (int ks = 0; ks < C::NKS; ++ks) {
-    settle(qf[ks]);
-    settle(wf[ks][0]);
-    settle(wf[ks][1]);
-  }
-  settle(ct);
+  for (int ks = 0; ks < C::NKS; ++ks) settle(qf[ks]);
   settle(l2);
 
-  f32x16 dqt[NB], sat[NB];  // (d or j block) x queries qh*32.., partial over this wave's keys
+  f32x16 acc[NB];  // (d or j block) x queries qh*32.., partial over this wave's keys: dQ^T or SA^T
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    dqt[b] = f32x16{};
-    sat[b] = f32x16{};
-  }
+  for (int b = 0; b < NB; ++b) acc[b] = f32x16{};
   float psum = 0.f;
   const float scale2 = kLog2e / sqrtf((float)D);
-  // Software pipeline over the key tiles, three LDS buffers.  Iteration kb
-  // runs the row-major products of tile kb (S^T = K Q^T, dP^T = Y (W U)^T)
-  // and the transposed products of tile kb - 1 (dQ^T += K^T dS^T,
-  // SA^T += Y^T P^T, with that tile's p and dS) in one basic block of
-  // independent MFMA chains, then forms p and dS of tile kb: the scheduler
-  // interleaves the chains, so the matrix pipe stays busy while operands
-  // arrive and while the vector units form p and dS.
-  constexpr int NG = 2 * NB;  // groups (d or j block, k-step) of the transposed products
-  bf16x8 ph[2] = {}, pl[2] = {}, dsb[2] = {};  // p hi / lo and dS of the tile before
-  auto tr_products = [&](int kb, int g0, int g1) {
-    const bf16* kt = &sm.key[kb % 3][0][0];
-    const bf16* ty = kt + kTile * D;
-    const bf16* tyl = ty + kTile * D;
-#pragma unroll
-    for (int g = g0; g < g1; ++g) {
-      const int b = g >> 1, k2 = g & 1, p0 = kh * 32 + k2 * 16;
-      const bf16x8 fk = frag_tr<D>(kt, b * 32, p0);
-      const bf16x8 fh = frag_tr<D>(ty, b * 32, p0);
-      const bf16x8 fl = frag_tr<D>(tyl, b * 32, p0);
-      dqt[b] = mfma(fk, dsb[k2], dqt[b]);
-      sat[b] = mfma(fh, ph[k2], sat[b]);
-      sat[b] = mfma(fl, ph[k2], sat[b]);
-      sat[b] = mfma(fh, pl[k2], sat[b]);
-    }
+  // Software pipeline over the key tiles, three LDS buffers: iteration kb runs
+  // the row-major products of tile kb and the transposed products of tile kb - 1.
+  // log2 p of accumulator row r of tile kb; masked: the diagonal tile, whose
+  // keys after the query (keys at or past T among them) drop out.  (A query
+  // row past T is an accumulator column of its own that is never stored.)
+  auto arg = [&](int kb, auto masked) __attribute__((always_inline)) {
+    const int lim = q0 + t - (kb * kTile + kh * 32 + 4 * hl);
+    return [=](int r, float s) __attribute__((always_inline)) {
+      const float x = fmaf(s, scale2, -l2);
+      if constexpr (decltype(masked)::value)
+        return 8 * (r >> 2) + (r & 3) <= lim ? x : -INFINITY;
+      else
+        return x;
+    };
   };
-  // one iteration; prev: whether tile kb - 1's transposed products run in
-  // it; masked: whether the tile pair needs the causal and length masks (only
-  // the diagonal tile, or a query tile that runs past T)
-  auto iteration = [&](int kb, auto prev, auto masked) {
-    const int k0 = kb * kTile;
+  auto next_tile = [&](int kb) {
     wait_vmem();
     __syncthreads();  // tile kb is in; every wave is done with tile kb - 2
-    if (kb < qb) fetch(kb + 1);
-    const bf16* kt = &sm.key[kb % 3][0][0];
-    const bf16* ty = kt + kTile * D;   // Y hi
-    const bf16* tyl = ty + kTile * D;  // Y lo
-    f32x16 s = {}, dp = {};
-#pragma unroll
-    for (int k = 0; k < C::NKS; ++k) s = mfma(frag_rows<D>(kt, kh * 32 + n, 2 * k + hl), qf[k], s);
-    if constexpr (decltype(prev)::value) tr_products(kb - 1, 0, NG / 2);
-#pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-      const bf16x8 ah = frag_rows<D>(ty, kh * 32 + n, 2 * ks + hl);
-      const bf16x8 al = frag_rows<D>(tyl, kh * 32 + n, 2 * ks + hl);
-      dp = mfma(ah, wf[ks][0], dp);
-      dp = mfma(al, wf[ks][0], dp);
-      dp = mfma(ah, wf[ks][1], dp);
-    }
-    if constexpr (decltype(prev)::value) tr_products(kb - 1, NG / 2, NG);
-    const bool tlive = q0 + t < T;
-    pack_p_ds(
-        [&](int r) {
-          const float x = fmaf(s[r], scale2, -l2);
-          float pr;
-          if constexpr (decltype(masked)::value) {
-            const int i = kh * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-            const bool ok = k0 + i <= q0 + t && tlive && k0 + i < T;
-            pr = exp2_hw(ok ? x : -INFINITY);
-          } else {
-            pr = exp2_hw(x);
-          }
-          psum += pr;
-          return f32x2{pr, ct};
-        },
-        dp, ph, pl, dsb);
   };
+  auto next_loads = [&](int kb) __attribute__((always_inline)) {
+    return [=](int x) __attribute__((always_inline)) {
+      if (kb < qb) fetch(kb + 1, x);
+    };
+  };
+  // iteration(kb, prev, masked) over the key tiles; prev: whether tile kb -
+  // 1's transposed products run in it; masked: the diagonal tile
   const std::true_type yes;
   const std::false_type no;
-  if (qb == 0) {
-    iteration(0, no, yes);
-  } else if (q0 + kTile <= T) {
-    iteration(0, no, no);
-    for (int kb = 1; kb < qb; ++kb) iteration(kb, yes, no);
-    iteration(qb, yes, yes);
-  } else {  // the query tile runs past T: every tile pair masks its rows
-    iteration(0, no, yes);
-    for (int kb = 1; kb <= qb; ++kb) iteration(kb, yes, yes);
+  auto walk = [&](auto&& iteration) __attribute__((always_inline)) {
+    if (qb == 0) {
+      iteration(0, no, yes);
+    } else {
+      iteration(0, no, no);
+      for (int kb = 1; kb < qb; ++kb) iteration(kb, yes, no);
+      iteration(qb, yes, yes);
+    }
+  };
+  if (role_dq) {
+    bf16x8 wf[C::NKS][2];  // W U hi / lo (for dP^T, zero past T)
+    {
+      const size_t wr = (rows0 + q0 + t) * D;
+#pragma unroll
+      for (int ks = 0; ks < C::NKS; ++ks) {
+        wf[ks][0] = *reinterpret_cast<const bf16x8*>(wh + wr + ks * 16 + hl * 8);
+        wf[ks][1] = *reinterpret_cast<const bf16x8*>(wl + wr + ks * 16 + hl * 8);
+      }
+    }
+    const float ct = cst[rows0 + q0 + t];
+#pragma unroll
+    for (int ks = 0; ks < C::NKS; ++ks) {
+      settle(wf[ks][0]);
+      settle(wf[ks][1]);
+    }
+    settle(ct);
+    f32x16 pv = {}, dp = {};  // p and dP of the tile before
+    const auto cc = [&](int) { return ct; };
+    walk([&](int kb, auto prev, auto masked) __attribute__((always_inline)) {
+      next_tile(kb);
+      step_ds<D, decltype(prev)::value>(rbase + buffer(kb), tbase + buffer(kb + 2), qf, wf, acc, pv,
+                                        dp, arg(kb, masked), cc, next_loads(kb));
+    });
+    finish_ds<D>(tbase + buffer(qb), acc, pv, dp, cc);
+  } else {
+    bf16x8 ph[2] = {}, pl[2] = {};  // p hi / lo of the tile before
+    const auto sum = [&](float p) { psum += p; };
+    walk([&](int kb, auto prev, auto masked) __attribute__((always_inline)) {
+      next_tile(kb);
+      step_p<D, decltype(prev)::value>(rbase + buffer(kb), tbase + buffer(kb + 2), qf, acc, ph, pl,
+                                       arg(kb, masked), sum, next_loads(kb));
+    });
+    finish_p<D>(tbase + buffer(qb), acc, ph, pl);
   }
-  tr_products(qb, 0, NG);
 
   // ---- epilogue.  The key halves (waves kh = 0, 1 of the same qh) meet in
   // LDS as [64 queries][D + 1] totals of dQ^T and SA^T; then every thread
@@ -979,29 +1186,22 @@ __global__ __launch_bounds__(kThreads) void bwd_q_fast_kernel(
   float* sas = dqs + kTile * SR;                             // [64][SR]
   static_assert(2 * kTile * (D + 1) * 4 <= sizeof(sm.key), "epilogue area");
   psum += __shfl_xor(psum, 32);
+  if (!role_dq && hl == 0) sm.pt[kh][t] = psum;
+  float* mine = role_dq ? dqs : sas;
   if (kh == 1) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-        dqs[t * SR + row] = dqt[b][r];
-        sas[t * SR + row] = sat[b][r];
-      }
-    if (hl == 0) sm.pt[1][t] = psum;
-  } else if (hl == 0) {
-    sm.pt[0][t] = psum;
+      for (int r = 0; r < 16; ++r)
+        mine[t * SR + b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3)] = acc[b][r];
   }
   __syncthreads();
   if (kh == 0) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-        dqs[t * SR + row] += dqt[b][r];
-        sas[t * SR + row] += sat[b][r];
-      }
+      for (int r = 0; r < 16; ++r)
+        mine[t * SR + b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3)] += acc[b][r];
   }
   __syncthreads();
   {
@@ -1009,7 +1209,7 @@ __global__ __launch_bounds__(kThreads) void bwd_q_fast_kernel(
     // may differ from the exact one by a few 2^-9: P = sum_i p rescales it
     const int j = tid % D;
     const float rs = 1.f / sqrtf((float)D);
-    for (int r = tid / D; r < kTile && q0 + r < T; r += kThreads / D) {
+    for (int r = tid / D; r < kTile && q0 + r < T; r += kFastWaves * 64 / D) {
       const float rP = 1.f / (sm.pt[0][r] + sm.pt[1][r]);
       const size_t at = base + (size_t)(q0 + r) * D + j;
       dQ[at] = dqs[r * SR + j] * rs * rP;
@@ -1111,9 +1311,12 @@ __global__ __launch_bounds__(kThreads) void bwd_prepq_kernel(
   }
 }
 
-// kv kernel, matrix-core form.  Wave (qh = w >> 1, kh = w & 1) owns the
-// 32 x 32 block (queries qh*32.., keys kh*32..) of each tile pair; its key
-// rows' operands (K and Y hi / lo as MFMA B fragments) stay in registers.
+// kv kernel, matrix-core form, in two roles like the q kernel: wave w and wave
+// w + 4 work on the same 32 x 32 block (queries qh*32.., keys kh*32..) of each
+// tile pair:
+//   dk (w < 4): dP = (W U') Y^T, dS, dK^T += Q^T dS; its key rows' K and Y
+//               hi / lo stay in registers as MFMA B fragments;
+//   dv (w >= 4): dV^T += (W U')^T P.
 template <int D>
 struct KvFast {
   bf16 qry[3][3][kTile * D];  // [buffer][Q, W U' hi, W U' lo], swizzled [query][d or j]
@@ -1121,7 +1324,7 @@ struct KvFast {
 };
 
 template <int D>
-__global__ __launch_bounds__(kThreads) void bwd_kv_fast_kernel(
+__global__ __launch_bounds__(kFastWaves * 64) void bwd_kv_fast_kernel(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ V,
     const float* __restrict__ beta, const float* __restrict__ lse, const float* __restrict__ cg,
     const bf16* __restrict__ yh, const bf16* __restrict__ yl, const bf16* __restrict__ wh,
@@ -1129,132 +1332,130 @@ __global__ __launch_bounds__(kThreads) void bwd_kv_fast_kernel(
     float* __restrict__ dV, float* __restrict__ vdv, int H, int T, int ntile) {
   using C = Bw<D>;
   constexpr int NB = C::NCB;  // 32-row blocks of d (and of j)
-  __shared__ __align__(16) KvFast<D> sm;
+  __shared__ __align__(256) KvFast<D> sm;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, n = lane & 31, hl = lane >> 5;
   const int lb = xcd_order(blockIdx.x, gridDim.x);
   const int kb = lb % ntile, bh = lb / ntile, h = bh % H;
   const int k0 = kb * kTile;
   const size_t base = (size_t)bh * T * D;
   const size_t rows0 = (size_t)bh * ntile * kTile;
-  const int qh = wave >> 1, kh = wave & 1;
-  auto fetch = [&](int qb) {
-    const int q0 = qb * kTile;
-    bf16* dst = &sm.qry[qb % 3][0][0];
-    load_swz<D>(Q + base + (size_t)q0 * D, dst, T - 1 - q0);
-    load_swz<D>(wh + (rows0 + q0) * D, dst + kTile * D, kTile - 1);
-    load_swz<D>(wl + (rows0 + q0) * D, dst + 2 * kTile * D, kTile - 1);
-    // row constants and log-normalisers: one dword per lane (rows past T re-read row T - 1)
-    if (wave == 0) dma4(cst + rows0 + q0 + lane, &sm.cst[qb % 3][0]);
-    if (wave == 1) dma4(lse + (size_t)bh * T + min(q0 + lane, T - 1), &sm.lse[qb % 3][0]);
+  const int qh = (wave >> 1) & 1, kh = wave & 1;
+  constexpr int AB = kTile * D * 2;  // bytes of one tile array
+  const unsigned lds0 = lds_addr(&sm.qry[0][0][0]);
+  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
+  const bool role_dk = wave_s < 4;
+  const unsigned loff = swz_lane<D>(wave, lane);
+  const unsigned rbase = rows_base<D>(qh * 32 + n, hl), tbase = tr_base<D>(qh * 32, lane);
+  auto buffer = [&](int qb) { return lds0 + (unsigned)(qb % 3) * (3 * AB); };
+  // load x (of kLoads) of query tile qb; with the first, the row constants and
+  // log-normalisers: one dword per lane (rows past T re-read row T - 1)
+  auto fetch = [&](int qb, int x) __attribute__((always_inline)) {
+    const int q0 = qb * kTile, a = x / kBlocksPerWave<D>;
+    const rsrc_t r = a == 0 ? buffer_rsrc(Q + base + (size_t)q0 * D, (unsigned)min(T - q0, kTile) * D * 2u)
+                            : buffer_rsrc((a == 1 ? wh : wl) + (rows0 + q0) * D, (unsigned)AB);
+    load_swz<D>(r, buffer(qb) + a * AB, wave_s, loff, x % kBlocksPerWave<D>);
+    if (x == 0) {
+      if (wave_s == 4) dma4(cst + rows0 + q0 + lane, &sm.cst[qb % 3][0]);
+      if (wave_s == 5) dma4(lse + (size_t)bh * T + min(q0 + lane, T - 1), &sm.lse[qb % 3][0]);
+    }
   };
-  fetch(kb);
+#pragma unroll
+  for (int x = 0; x < kLoads<D>; ++x) fetch(kb, x);
 
-  for (int j = tid; j < D; j += kThreads) {
+  for (int j = tid; j < D; j += kFastWaves * 64) {
     sm.bl[j] = beta[h * D + j] * kLog2e;
     sm.c[j] = cg[bh * D + j];
   }
   const int i = kh * 32 + n;
   // this wave's key rows as MFMA B fragments: K (for S; rows past T re-read
-  // row T - 1, their p is masked) and Y hi / lo (for dP, zero past T),
-  // loop-invariant
-  bf16x8 kf[C::NKS], yf[C::NKS][2];
+  // row T - 1, their p is masked), loop-invariant
+  bf16x8 kf[C::NKS];
   {
-    const size_t kr = base + (size_t)min(k0 + i, T - 1) * D, yr = (rows0 + k0 + i) * D;
+    const size_t kr = base + (size_t)min(k0 + i, T - 1) * D;
 #pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
+    for (int ks = 0; ks < C::NKS; ++ks)
       kf[ks] = *reinterpret_cast<const bf16x8*>(K + kr + ks * 16 + hl * 8);
-      yf[ks][0] = *reinterpret_cast<const bf16x8*>(yh + yr + ks * 16 + hl * 8);
-      yf[ks][1] = *reinterpret_cast<const bf16x8*>(yl + yr + ks * 16 + hl * 8);
-    }
 #pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-      settle(kf[ks]);
-      settle(yf[ks][0]);
-      settle(yf[ks][1]);
-    }
+    for (int ks = 0; ks < C::NKS; ++ks) settle(kf[ks]);
   }
 
-  f32x16 dvt[NB], dkt[NB];  // (j or d block) x keys kh*32.., partial over this wave's queries
+  f32x16 acc[NB];  // (d or j block) x keys kh*32.., partial over this wave's queries: dK^T or dV^T
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    dvt[b] = f32x16{};
-    dkt[b] = f32x16{};
-  }
+  for (int b = 0; b < NB; ++b) acc[b] = f32x16{};
   const float scale2 = kLog2e / sqrtf((float)D);
   const int qlast = (T - 1) / kTile;
-  // Software pipeline over the query tiles, three LDS buffers, as in the q
-  // pass: iteration qb runs S = Q K^T and dP = (W U') Y^T of tile qb and the
-  // transposed products of tile qb - 1 (dV^T += (W U')^T P, dK^T += Q^T dS)
-  // in one basic block, then forms p and dS of tile qb.
-  constexpr int NG = 2 * NB;
-  bf16x8 ph[2] = {}, pl[2] = {}, dsb[2] = {};  // p hi / lo and dS of the tile before
-  auto tr_products = [&](int qb, int g0, int g1) {
-    const bf16* tq = &sm.qry[qb % 3][0][0];
-    const bf16* tw = tq + kTile * D;
-    const bf16* twl = tw + kTile * D;
-#pragma unroll
-    for (int g = g0; g < g1; ++g) {
-      const int b = g >> 1, k2 = g & 1, p0 = qh * 32 + k2 * 16;
-      const bf16x8 gh = frag_tr<D>(tw, b * 32, p0);
-      const bf16x8 gl = frag_tr<D>(twl, b * 32, p0);
-      const bf16x8 fq = frag_tr<D>(tq, b * 32, p0);
-      dvt[b] = mfma(gh, ph[k2], dvt[b]);
-      dvt[b] = mfma(gl, ph[k2], dvt[b]);
-      dvt[b] = mfma(gh, pl[k2], dvt[b]);
-      dkt[b] = mfma(fq, dsb[k2], dkt[b]);
-    }
+  // Software pipeline over the query tiles, three LDS buffers, as in the q pass.
+  // rows(x, r): entry of accumulator row r of a per-query table
+  auto rows = [&](const float* x, int r) { return x[qh * 32 + 8 * (r >> 2) + 4 * hl + (r & 3)]; };
+  // log2 p of accumulator row r of tile qb, masked or not: query row r0 + step(r)
+  // lies in [key, T) for r's step within `span` of `lo`
+  auto arg = [&](int qb, auto masked) __attribute__((always_inline)) {
+    const float* lq = sm.lse[qb % 3];
+    const int r0 = qb * kTile + qh * 32 + 4 * hl, key = k0 + i;
+    const int lo = key - r0;
+    const unsigned span = (unsigned)max(T - key, 0);
+    return [=](int r, float s) __attribute__((always_inline)) {
+      const float x = fmaf(s, scale2, -rows(lq, r) * kLog2e);
+      if constexpr (decltype(masked)::value)
+        return (unsigned)(8 * (r >> 2) + (r & 3) - lo) < span ? x : -INFINITY;
+      else
+        return x;
+    };
   };
-  // one iteration; prev: whether tile qb - 1's transposed products run in
-  // it; masked: whether the tile pair needs the causal and length masks (the
-  // diagonal tile, or a tile that runs past T)
-  auto iteration = [&](int qb, auto prev, auto masked) {
-    const int q0 = qb * kTile;
+  auto next_tile = [&](int qb) {
     wait_vmem();
     __syncthreads();  // tile qb is in; every wave is done with tile qb - 2
-    if (qb < qlast) fetch(qb + 1);
-    const bf16* tq = &sm.qry[qb % 3][0][0];
-    const bf16* tw = tq + kTile * D;   // W U' hi
-    const bf16* twl = tw + kTile * D;  // W U' lo
-    const float* lq = sm.lse[qb % 3];
-    const float* cq = sm.cst[qb % 3];
-    f32x16 s = {}, dp = {};
-#pragma unroll
-    for (int k = 0; k < C::NKS; ++k) s = mfma(frag_rows<D>(tq, qh * 32 + n, 2 * k + hl), kf[k], s);
-    if constexpr (decltype(prev)::value) tr_products(qb - 1, 0, NG / 2);
-#pragma unroll
-    for (int ks = 0; ks < C::NKS; ++ks) {
-      const bf16x8 ah = frag_rows<D>(tw, qh * 32 + n, 2 * ks + hl);
-      const bf16x8 al = frag_rows<D>(twl, qh * 32 + n, 2 * ks + hl);
-      dp = mfma(ah, yf[ks][0], dp);
-      dp = mfma(al, yf[ks][0], dp);
-      dp = mfma(ah, yf[ks][1], dp);
-    }
-    if constexpr (decltype(prev)::value) tr_products(qb - 1, NG / 2, NG);
-    pack_p_ds(
-        [&](int r) {
-          const int t = qh * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-          const float x = fmaf(s[r], scale2, -lq[t] * kLog2e);
-          float pr;
-          if constexpr (decltype(masked)::value) {
-            const bool ok = k0 + i <= q0 + t && q0 + t < T && k0 + i < T;
-            pr = exp2_hw(ok ? x : -INFINITY);
-          } else {
-            pr = exp2_hw(x);
-          }
-          return f32x2{pr, cq[t]};
-        },
-        dp, ph, pl, dsb);
   };
+  auto next_loads = [&](int qb) __attribute__((always_inline)) {
+    return [=](int x) __attribute__((always_inline)) {
+      if (qb < qlast) fetch(qb + 1, x);
+    };
+  };
+  // iteration(qb, prev, masked); prev: whether tile qb - 1's transposed
+  // products run in it; masked: the tile pair takes the causal and length
+  // masks (the diagonal tile, and the last one, which may run past T)
   const std::true_type yes;
   const std::false_type no;
-  const bool ragged = qlast * kTile + kTile > T;  // the last query tile runs past T
-  iteration(kb, no, yes);
-  for (int qb = kb + 1; qb < qlast; ++qb) iteration(qb, yes, no);
-  if (qlast > kb) {
-    if (ragged) iteration(qlast, yes, yes);
-    else iteration(qlast, yes, no);
+  auto walk = [&](auto&& iteration) __attribute__((always_inline)) {
+    iteration(kb, no, yes);
+    for (int qb = kb + 1; qb < qlast; ++qb) iteration(qb, yes, no);
+    if (qlast > kb) iteration(qlast, yes, yes);
+  };
+  if (role_dk) {
+    bf16x8 yf[C::NKS][2];  // Y hi / lo (for dP, zero past T)
+    {
+      const size_t yr = (rows0 + k0 + i) * D;
+#pragma unroll
+      for (int ks = 0; ks < C::NKS; ++ks) {
+        yf[ks][0] = *reinterpret_cast<const bf16x8*>(yh + yr + ks * 16 + hl * 8);
+        yf[ks][1] = *reinterpret_cast<const bf16x8*>(yl + yr + ks * 16 + hl * 8);
+      }
+#pragma unroll
+      for (int ks = 0; ks < C::NKS; ++ks) {
+        settle(yf[ks][0]);
+        settle(yf[ks][1]);
+      }
+    }
+    f32x16 pv = {}, dp = {};  // p and dP of the tile before
+    const auto cc = [&](int qb) __attribute__((always_inline)) {
+      const float* cq = sm.cst[qb % 3];
+      return [=](int r) __attribute__((always_inline)) { return rows(cq, r); };
+    };
+    walk([&](int qb, auto prev, auto masked) __attribute__((always_inline)) {
+      next_tile(qb);
+      step_ds<D, decltype(prev)::value>(rbase + buffer(qb), tbase + buffer(qb + 2), kf, yf, acc, pv,
+                                        dp, arg(qb, masked), cc(qb + 2), next_loads(qb));
+    });
+    finish_ds<D>(tbase + buffer(qlast), acc, pv, dp, cc(qlast));
+  } else {
+    bf16x8 ph[2] = {}, pl[2] = {};  // p hi / lo of the tile before
+    walk([&](int qb, auto prev, auto masked) __attribute__((always_inline)) {
+      next_tile(qb);
+      step_p<D, decltype(prev)::value>(rbase + buffer(qb), tbase + buffer(qb + 2), kf, acc, ph, pl,
+                                       arg(qb, masked), [](float) {}, next_loads(qb));
+    });
+    finish_p<D>(tbase + buffer(qlast), acc, ph, pl);
   }
-  tr_products(qlast, 0, NG);
 
   // ---- epilogue.  The query halves (waves qh = 0, 1 of the same kh) meet
   // in LDS as [64 keys][D + 1] totals of dV^T and dK^T; then every thread
@@ -1264,28 +1465,24 @@ __global__ __launch_bounds__(kThreads) void bwd_kv_fast_kernel(
   constexpr int SR = D + 1;
   float* dvs = reinterpret_cast<float*>(&sm.qry[0][0][0]);  // [64][SR]
   float* dks = dvs + kTile * SR;                             // [64][SR]
-  float* vpart = dks + kTile * SR;                           // [kThreads]
-  static_assert((2 * kTile * (D + 1) + kThreads) * 4 <= sizeof(sm.qry), "epilogue area");
+  constexpr int NT = kFastWaves * 64;
+  float* vpart = dks + kTile * SR;                           // [NT]
+  static_assert((2 * kTile * (D + 1) + NT) * 4 <= sizeof(sm.qry), "epilogue area");
+  float* mine = role_dk ? dks : dvs;
   if (qh == 1) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-        dvs[i * SR + row] = dvt[b][r];
-        dks[i * SR + row] = dkt[b][r];
-      }
+      for (int r = 0; r < 16; ++r)
+        mine[i * SR + b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3)] = acc[b][r];
   }
   __syncthreads();
   if (qh == 0) {
 #pragma unroll
     for (int b = 0; b < NB; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int row = b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3);
-        dvs[i * SR + row] += dvt[b][r];
-        dks[i * SR + row] += dkt[b][r];
-      }
+      for (int r = 0; r < 16; ++r)
+        mine[i * SR + b * 32 + 8 * (r >> 2) + 4 * hl + (r & 3)] += acc[b][r];
   }
   __syncthreads();
   {
@@ -1293,7 +1490,7 @@ __global__ __launch_bounds__(kThreads) void bwd_kv_fast_kernel(
     const float cj = sm.c[j], blj = sm.bl[j], bj = beta[h * D + j];
     const float rs = 1.f / sqrtf((float)D);
     float vacc = 0.f;
-    for (int r = tid / D; r < kTile && k0 + r < T; r += kThreads / D) {
+    for (int r = tid / D; r < kTile && k0 + r < T; r += NT / D) {
       const size_t at = base + (size_t)(k0 + r) * D + j;
       const float vv = (float)V[at];
       // dV = beta E sum_t p (W U'), E = 2^{bl v - c}
@@ -1307,7 +1504,7 @@ __global__ __launch_bounds__(kThreads) void bwd_kv_fast_kernel(
   __syncthreads();
   if (tid < D) {
     float acc = 0.f;
-    for (int g = 0; g < kThreads / D; ++g) acc += vpart[g * D + tid];
+    for (int g = 0; g < NT / D; ++g) acc += vpart[g * D + tid];
     vdv[((size_t)bh * ntile + kb) * D + tid] = acc;
   }
 }
@@ -1409,7 +1606,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const float* 
     e = hipGetLastError();
   }
   if (e == hipSuccess) {  // the q pass first: its SA / P give ln(Z/P), which the kv pass uses
-    hipLaunchKernelGGL(bwd_q_fast_kernel<D>, grid, blk, 0, stream, q, k, lse_fwd, yh, yl, wh, wl,
+    hipLaunchKernelGGL(bwd_q_fast_kernel<D>, grid, dim3(kFastWaves * 64), 0, stream, q, k, lse_fwd, yh, yl, wh, wl,
                        cst, dQ, sap, lse, T, ntile);
     e = hipGetLastError();
   }
@@ -1419,7 +1616,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const float* 
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(bwd_kv_fast_kernel<D>, grid, blk, 0, stream, q, k, v, beta, lse, cg, yh, yl,
+    hipLaunchKernelGGL(bwd_kv_fast_kernel<D>, grid, dim3(kFastWaves * 64), 0, stream, q, k, v, beta, lse, cg, yh, yl,
                        wh, wl, cst, dK, dV, vdv, H, T, ntile);
     e = hipGetLastError();
   }
