@@ -1512,34 +1512,52 @@ __global__ __launch_bounds__(kFastWaves * 64) void bwd_kv_fast_kernel(
 // dbeta from the per-tile partial sums: the element-wise pass's for the
 // channels it took (every channel, or the wide ones of a (b, h)), else
 // (sum v dV - sum G F) / beta from the matrix-core pass.  One workgroup per
-// (h, 32 channels); its 8 thread rows split the (b, tile) partials and meet
-// in LDS.
+// (h, 32 channels); its 32 thread rows split the (b, tile) partials, four
+// loads of each kind in flight, and meet in LDS.  Only H d / 32 workgroups,
+// so latency bounds it: at H16 d128 and 512 partials 59 us with 8 rows and one
+// partial at a time, 9 us so.
+constexpr int kDbRows = 32;
+
 template <int D>
-__global__ __launch_bounds__(256) void dbeta_kernel(const float* __restrict__ exact,
-                                                    const float* __restrict__ vdv,
-                                                    const float* __restrict__ gf,
-                                                    const float* __restrict__ beta,
-                                                    const int* __restrict__ flag,
-                                                    const float* __restrict__ splitf,
-                                                    float* __restrict__ dbeta, int B, int H,
-                                                    int ntile) {
-  __shared__ double part[8][32];
+__global__ __launch_bounds__(32 * kDbRows) void dbeta_kernel(const float* __restrict__ exact,
+                                                             const float* __restrict__ vdv,
+                                                             const float* __restrict__ gf,
+                                                             const float* __restrict__ beta,
+                                                             const int* __restrict__ flag,
+                                                             const float* __restrict__ splitf,
+                                                             float* __restrict__ dbeta, int B,
+                                                             int H, int ntile) {
+  constexpr int U = 4;
+  __shared__ double part[kDbRows][32];
   const int h = blockIdx.x, j = blockIdx.y * 32 + (threadIdx.x & 31), row = threadIdx.x >> 5;
   const bool all = flag[0] != 0;
+  const int n = B * ntile;
   double se = 0.0, sm = 0.0;  // element-wise partials; matrix-core partials (times beta)
-  for (int u = row; u < B * ntile; u += 8) {
-    const int b = u / ntile, c = u % ntile;
-    const size_t at = (((size_t)b * H + h) * ntile + c) * D + j;
-    if (all || splitf[((size_t)b * H + h) * D + j] == kWide)
-      se += (double)exact[at];
-    else
-      sm += (double)vdv[at] - (double)gf[at];
+  for (int u0 = row; u0 < n; u0 += U * kDbRows) {
+    float x[U], y[U], w[U];
+    size_t at[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      const int u = min(u0 + i * kDbRows, n - 1), b = u / ntile;
+      at[i] = (((size_t)b * H + h) * ntile + (u - b * ntile)) * D + j;
+      x[i] = vdv[at[i]];
+      y[i] = gf[at[i]];
+      w[i] = splitf[((size_t)b * H + h) * D + j];
+    }
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+      if (u0 + i * kDbRows >= n) break;
+      if (all || w[i] == kWide)
+        se += (double)exact[at[i]];
+      else
+        sm += (double)x[i] - (double)y[i];
+    }
   }
   double s = se + sm / (double)beta[h * D + j];
   part[row][threadIdx.x & 31] = s;
   __syncthreads();
   if (row == 0) {
-    for (int r = 1; r < 8; ++r) s += part[r][threadIdx.x & 31];
+    for (int r = 1; r < kDbRows; ++r) s += part[r][threadIdx.x & 31];
     dbeta[h * D + j] = (float)s;
   }
 }
@@ -1638,7 +1656,7 @@ hipError_t launch_bwd(const void* Q, const void* K, const void* V, const float* 
     e = hipGetLastError();
   }
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(dbeta_kernel<D>, dim3((unsigned)H, D / 32), dim3(256), 0, stream, exact, vdv,
+    hipLaunchKernelGGL(dbeta_kernel<D>, dim3((unsigned)H, D / 32), dim3(32 * kDbRows), 0, stream, exact, vdv,
                        gfp, beta, flag, splitf, dbeta, B, H, ntile);
     e = hipGetLastError();
   }
