@@ -22,6 +22,18 @@ hipError_t launch_softmax_train_bf16(const void* Q, const void* K, const void* V
                                      const float* beta, float* out, float* lse, int B, int H,
                                      int T, int d, hipStream_t stream);
 
+// The launches of one pair of widths, each instantiated in a source file of
+// its own (fem_softmax_*.hip); lse may be null, gate may be null (g = 1).
+#define FEM_SOFTMAX_ARGS                                                                        \
+  const void *Q, const void *K, const void *V, const float *beta, int B, int H, int T,          \
+      hipStream_t stream
+template <int DK, int DV>
+hipError_t softmax_causal(FEM_SOFTMAX_ARGS, void* out, bool obf16, float* lse);
+template <int DK, int DV>
+hipError_t softmax_encoder(FEM_SOFTMAX_ARGS, void* out, bool obf16);
+template <int D>
+hipError_t softmax_gated(FEM_SOFTMAX_ARGS, const float* lam, const float* gate, float* out);
+
 // Backward of the causal softmax-prior read (bf16 inputs, d in {32, 64, 128}).
 // ws holds at least softmax_bwd_ws_bytes(B, H, T, d) bytes, 256-byte aligned.
 size_t softmax_bwd_ws_bytes(int B, int H, int T, int d);
