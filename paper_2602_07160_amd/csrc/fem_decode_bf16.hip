@@ -16,14 +16,14 @@
 // v_{i,j} (log2 units) with its own running maximum, and the read is
 // LSE_j(x) - LSE(s), so there is no shared shift and no underflow case.
 //
-// Split-K: workgroup (split, b*H + h) covers keys [split*SL, (split+1)*SL)
+// Split-K: workgroup (b*H + h) * S + split covers keys [split*SL, (split+1)*SL)
 // in blocks of 64, with the next block's K and V already loading while the
 // current one is reduced.  Per block, four lanes form each of the 64 scores
 // (a quarter of the dot product each, then two lane swaps); then each lane
 // takes 8 consecutive channels of a few keys (16-byte V loads) and folds them
 // into its running (max, sum) pairs.  The split's pairs are merged through
 // LDS and written to a workspace; a second kernel merges the splits and
-// forms the read.
+// forms the read.  With one split per (b, h) the first kernel forms it.
 
 #include "fem_device.h"
 #include "fem_internal.h"
@@ -55,20 +55,31 @@ __device__ __forceinline__ void lse_merge(float& M, float& S, float m2, float s2
   M = mn;
 }
 
-template <int DK, int DV>
+// The read from the joint and the prior's log-sum-exps.
+__device__ __forceinline__ float decode_read(float Mj, float Sj, float md, float sd, float bl) {
+  return ((Mj - md) + (log2_hw(Sj) - log2_hw(sd))) / bl;
+}
+
+// Keys of sequence b that its step reads (0 for an invalid length).
+__device__ __forceinline__ int decode_keys(const int* lens, int b, int L) {
+  const int n = lens ? lens[b] : L;
+  return n >= 1 && n <= L ? n : 0;
+}
+// FINAL: one split per (b, h), which writes the read to `out`; else the
+// partial results go to ws.
+template <int DK, int DV, bool FINAL>
 __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
     const bf16* __restrict__ q, const bf16* __restrict__ Kc, const bf16* __restrict__ Vc,
-    const int* __restrict__ lens, const float* __restrict__ beta, float2* __restrict__ ws, int H,
-    int L, int nsplit, int bps) {
+    const int* __restrict__ lens, const float* __restrict__ beta, float2* __restrict__ ws,
+    float* __restrict__ out, int H, int L, int nsplit, int bps) {
   using C = Dec<DK, DV>;
   __shared__ float sc[2][kBlk];                 // block scores (log2 units)
   __shared__ float2 part[C::NGRP][DV + 1];      // per key group: channels, then the scores
 
   const int tid = threadIdx.x;
-  const int split = blockIdx.x, bh = blockIdx.y;
+  const int bh = blockIdx.x / nsplit, split = blockIdx.x % nsplit;
   const int b = bh / H, h = bh % H;
-  const int n0 = lens ? lens[b] : L;
-  const int n = (n0 >= 1 && n0 <= L) ? n0 : 0;  // an invalid length reads nothing
+  const int n = decode_keys(lens, b, L);  // an invalid length reads nothing
   const int kbeg = split * bps * kBlk;
   const int kend = min(n, kbeg + bps * kBlk);
   const int nblk = kend > kbeg ? (kend - kbeg + kBlk - 1) / kBlk : 0;
@@ -179,30 +190,100 @@ __global__ __launch_bounds__(kThreads) void decode_partial_kernel(
   for (int e = 0; e < 8; ++e) part[grp][oc * 8 + e] = make_float2(M[e], S[e]);
   if (oc == 0) part[grp][DV] = make_float2(md, sd);
   __syncthreads();
-  for (int j = tid; j <= DV; j += kThreads) {
-    float Mj = -INFINITY, Sj = 0.f;
+  float2* w = ws + ((size_t)bh * nsplit + split) * (DV + 1);
+  float Mj = -INFINITY, Sj = 0.f;
+  for (int j = tid; j <= DV; j += kThreads) {  // (DV < kThreads: at most one column a thread)
     for (int g = 0; g < C::NGRP; ++g) lse_merge(Mj, Sj, part[g][j].x, part[g][j].y);
-    ws[((size_t)bh * nsplit + split) * (DV + 1) + j] = make_float2(Mj, Sj);
+    if (!FINAL) w[j] = make_float2(Mj, Sj);
+    if (FINAL && j == DV) part[0][DV] = make_float2(Mj, Sj);
+  }
+  if constexpr (FINAL) {
+    __syncthreads();
+    static_assert(DV < kThreads, "one channel per thread");
+    if (tid < DV) {
+      const float2 d = part[0][DV];
+      const float o = decode_read(Mj, Sj, d.x, d.y, beta[h * DV + tid] * kLog2e);
+      out[(size_t)bh * DV + tid] = n > 0 ? o : NAN;
+    }
   }
 }
 
+// Merge of the splits of one (b, h).  Up to kMergeFew splits, one thread a
+// channel takes them in turn; more, blockDim / DV thread groups take every so
+// manieth split, kMergeBatch loads in flight, and meet in LDS, and the prior's
+// normaliser is merged by the lanes of each wave, one split each.  Latency
+// bounds both: in turn ~0.7 us a split (2 splits 4.1 us and 4.9 in parallel;
+// 5 splits 5.4 and 4.0; 11 8.5 and 4.0; 128 68 and 4.5).
+constexpr int kMergeFew = 3;
+constexpr int kMergeBatch = 8;
+constexpr int kMergeMax = 1024;  // threads
+
 template <int DV>
-__global__ __launch_bounds__(kThreads) void decode_merge_kernel(
+__global__ __launch_bounds__(DV < 64 ? 64 : DV) void decode_merge_few_kernel(
     const float2* __restrict__ ws, const int* __restrict__ lens, const float* __restrict__ beta,
     float* __restrict__ out, int H, int L, int nsplit) {
-  const int bh = blockIdx.x;
-  const int b = bh / H, h = bh % H;
-  const int n0 = lens ? lens[b] : L;
-  const bool valid = n0 >= 1 && n0 <= L;
+  const int bh = blockIdx.x, b = bh / H, h = bh % H, j = threadIdx.x;
+  if (j >= DV) return;
   const float2* w = ws + (size_t)bh * nsplit * (DV + 1);
+  float M = -INFINITY, S = 0.f, md = -INFINITY, sd = 0.f;
+  for (int s = 0; s < nsplit; ++s) {
+    const float2 x = w[s * (DV + 1) + j], d = w[s * (DV + 1) + DV];
+    lse_merge(M, S, x.x, x.y);
+    lse_merge(md, sd, d.x, d.y);
+  }
+  const float o = decode_read(M, S, md, sd, beta[h * DV + j] * kLog2e);
+  out[(size_t)bh * DV + j] = decode_keys(lens, b, L) > 0 ? o : NAN;
+}
+
+template <int DV>
+__global__ __launch_bounds__(kMergeMax) void decode_merge_kernel(
+    const float2* __restrict__ ws, const int* __restrict__ lens, const float* __restrict__ beta,
+    float* __restrict__ out, int H, int L, int nsplit) {
+  __shared__ float2 part[kMergeMax / DV][DV];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int bh = blockIdx.x, b = bh / H, h = bh % H;
+  const bool valid = decode_keys(lens, b, L) > 0;
+  const int cnt = nsplit;
+  const float2* w = ws + (size_t)bh * cnt * (DV + 1);
+  const int j = tid % DV, grp = tid / DV, ngrp = blockDim.x / DV;
+  const float bl = beta[h * DV + j] * kLog2e;
   float md = -INFINITY, sd = 0.f;
-  for (int s = 0; s < nsplit; ++s) lse_merge(md, sd, w[s * (DV + 1) + DV].x, w[s * (DV + 1) + DV].y);
-  for (int j = threadIdx.x; j < DV; j += kThreads) {
-    float Mj = -INFINITY, Sj = 0.f;
-    for (int s = 0; s < nsplit; ++s) lse_merge(Mj, Sj, w[s * (DV + 1) + j].x, w[s * (DV + 1) + j].y);
-    const float bl = beta[h * DV + j] * kLog2e;
-    const float o = ((Mj - md) + (log2_hw(Sj) - log2_hw(sd))) / bl;
-    out[(size_t)bh * DV + j] = valid ? o : NAN;
+  for (int s0 = 0; s0 < cnt; s0 += 64) {
+    if (s0 + lane < cnt) {
+      const float2 x = w[(size_t)(s0 + lane) * (DV + 1) + DV];
+      lse_merge(md, sd, x.x, x.y);
+    }
+  }
+  float M = -INFINITY, S = 0.f;
+  for (int s0 = grp; s0 < cnt; s0 += kMergeBatch * ngrp) {
+    float2 x[kMergeBatch];
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i) {
+      const int sp = s0 + i * ngrp;
+      x[i] = w[(size_t)min(sp, cnt - 1) * (DV + 1) + j];
+      if (sp >= cnt) x[i] = make_float2(-INFINITY, 0.f);
+    }
+    float mb = x[0].x;
+#pragma unroll
+    for (int i = 1; i < kMergeBatch; ++i) mb = fmaxf(mb, x[i].x);
+    if (mb == -INFINITY) continue;
+    float sb = 0.f;
+#pragma unroll
+    for (int i = 0; i < kMergeBatch; ++i) sb += x[i].y * exp2_hw(x[i].x - mb);
+    lse_merge(M, S, mb, sb);
+  }
+  {
+    const float mm = wave_max(md);
+    sd = md == -INFINITY ? 0.f : sd * exp2_hw(md - mm);
+    sd = wave_sum(sd);
+    md = mm;
+  }
+  part[grp][j] = make_float2(M, S);
+  __syncthreads();
+  if (tid < DV) {
+    for (int g = 1; g < ngrp; ++g) lse_merge(M, S, part[g][tid].x, part[g][tid].y);
+    const float o = decode_read(M, S, md, sd, bl);
+    out[(size_t)bh * DV + tid] = valid ? o : NAN;
   }
 }
 
@@ -232,13 +313,27 @@ hipError_t launch_decode(const void* q, const void* Kc, const void* Vc, const in
   decode_splits(B, H, L, &nsplit, &bps);
   if (nsplit > 65535 || nbh > 65535) return hipErrorInvalidValue;
   float2* ws = static_cast<float2*>(wsv);  // partials [nbh][nsplit][DV + 1]
-  hipLaunchKernelGGL((decode_partial_kernel<DK, DV>), dim3((unsigned)nsplit, (unsigned)nbh),
-                     dim3(kThreads), 0, stream, reinterpret_cast<const bf16*>(q),
-                     reinterpret_cast<const bf16*>(Kc), reinterpret_cast<const bf16*>(Vc), lens,
-                     beta, ws, H, L, nsplit, bps);
+  const bf16* qb = reinterpret_cast<const bf16*>(q);
+  const bf16* kb = reinterpret_cast<const bf16*>(Kc);
+  const bf16* vb = reinterpret_cast<const bf16*>(Vc);
+  const dim3 grid((unsigned)(nbh * nsplit)), block(kThreads);
+  if (nsplit == 1) {  // no merge
+    hipLaunchKernelGGL((decode_partial_kernel<DK, DV, true>), grid, block, 0, stream, qb, kb, vb,
+                       lens, beta, ws, out, H, L, nsplit, bps);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((decode_partial_kernel<DK, DV, false>), grid, block, 0, stream, qb, kb, vb,
+                     lens, beta, ws, out, H, L, nsplit, bps);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL((decode_merge_kernel<DV>), dim3((unsigned)nbh), dim3(kThreads), 0, stream,
+  if (e == hipSuccess && nsplit <= kMergeFew) {
+    hipLaunchKernelGGL((decode_merge_few_kernel<DV>), dim3((unsigned)nbh),
+                       dim3(DV < 64 ? 64 : DV), 0, stream, ws, lens, beta, out, H, L, nsplit);
+    e = hipGetLastError();
+  } else if (e == hipSuccess) {
+    // enough thread groups for one batch of splits each
+    const int want = DV * ((nsplit + kMergeBatch - 1) / kMergeBatch);
+    const int threads = want <= 256 ? 256 : want <= 512 ? 512 : kMergeMax;
+    hipLaunchKernelGGL((decode_merge_kernel<DV>), dim3((unsigned)nbh), dim3(threads), 0, stream,
                        ws, lens, beta, out, H, L, nsplit);
     e = hipGetLastError();
   }
