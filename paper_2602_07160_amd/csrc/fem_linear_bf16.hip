@@ -872,7 +872,12 @@ __device__ __forceinline__ void scan_chunk(ScanSmem<PRIOR, CH, NSUB>& sm, f32x16
 // per state entry: S[j][*] carries row shift c_j, z needs none, c is the max.
 // GLA: the state entering segment s+1 is the one entering s, decayed by the
 // total log-decay of segment s along its key channel, plus the own state of s.
-template <int PRIOR>
+// Latency bounds it, one of loads per batch of PB segments: up to kPrefixFew
+// segments take one batch of 8, up to kPrefixOne one of 32 (GLA, 20 segments
+// of 24 (b, h): 11.7 us in batches of 8, 8.1 so, 32 in prefix_wide_kernel, most
+// of whose groups would be idle); prefix_wide_kernel takes more.
+constexpr int kPrefixFew = 9, kPrefixOne = 33;
+template <int PRIOR, int PB>
 __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ own,
                                                      float* __restrict__ pre, int nseg) {
   constexpr int SF = state_floats<PRIOR>();
@@ -886,7 +891,6 @@ __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ o
   const int kc = e < DV * DK ? e % DK : (e < DV * DK + DK ? e - DV * DK : -1);
   // segments in batches of PB: every load of a batch is issued before the
   // batch's (sequential) combination
-  constexpr int PB = 8;
   float acc = 0.f, C = -INFINITY;
   for (int s0 = 0; s0 + 1 < nseg; s0 += PB) {
     float val[PB], cs[PB], lg[PB];
@@ -914,6 +918,88 @@ __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ o
       }
       pb[(size_t)(sg + 1) * SF + e] = acc;
     }
+  }
+}
+
+// The same prefix for many segments, the segments split over thread groups:
+// group g of a workgroup takes PB consecutive ones of every round of NG PB,
+// sums them from zero, reads the groups before it from LDS and then walks its
+// own again from the state that enters them.  A round costs one latency of
+// loads instead of one per batch: 128 segments of one (b, h) 26.9 us in batches
+// of 32 and 8.5 so, of four (b, h) 33.2 and 12.5.
+constexpr int PNG = 8, PPB = 16, PEN = NTH / PNG;  // groups, segments, entries
+static_assert(STATE % PEN == 0, "whole workgroups of entries");
+
+// 2^(x - m) for x <= m, 1 where they are equal (both may be -inf: nothing yet)
+__device__ __forceinline__ float weight(float x, float m) { return x == m ? 1.f : exp2_hw(x - m); }
+
+template <int PRIOR>
+__global__ __launch_bounds__(NTH) void prefix_wide_kernel(const float* __restrict__ own,
+                                                          float* __restrict__ pre, int nseg) {
+  constexpr int SF = state_floats<PRIOR>();
+  __shared__ float sa[PNG][PEN], sc[PNG][PEN], sl[PNG][PEN];
+  const int g = threadIdx.x / PEN, le = threadIdx.x % PEN;
+  const int e = blockIdx.x * PEN + le;
+  const size_t base = (size_t)blockIdx.y * nseg * SF;
+  const float* ob = own + base;
+  float* pb = pre + base;
+  const bool is_s = e < DV * DK, is_c = e >= DV * DK + DK;  // S entry, shift entry (else z)
+  const bool has_decay = PRIOR == kGla && !is_c;
+  const int kc = is_s ? e % DK : e - DV * DK;
+  // (acc, C) followed by a part (val, c) whose keys decay the earlier ones by 2^lg
+  const auto join = [&](float& acc, float& C, float val, float c, float lg) {
+    if (is_c) {
+      acc = fmaxf(acc, val);
+      return;
+    }
+    if (has_decay) acc *= exp2_hw(lg);
+    if (is_s) {
+      const float Cn = fmaxf(C, c);
+      acc = acc * weight(C, Cn) + val * weight(c, Cn);
+      C = Cn;
+    } else {
+      acc += val;
+    }
+  };
+  const float zero = is_c ? -INFINITY : 0.f;
+  float acc = zero, C = -INFINITY;  // the state that enters the round
+  for (int r0 = 0; r0 + 1 < nseg; r0 += PNG * PPB) {
+    const int s0 = r0 + g * PPB;
+    float val[PPB], cs[PPB], lg[PPB];
+#pragma unroll
+    for (int u = 0; u < PPB; ++u) {
+      const bool in = s0 + u + 1 < nseg;  // (past the end: an empty part)
+      const size_t o = (size_t)(s0 + u) * SF;
+      val[u] = in ? ob[o + e] : zero;
+      cs[u] = in && is_s ? ob[o + DV * DK + DK + e / DK] : -INFINITY;
+      lg[u] = in && has_decay ? ob[o + STATE + kc] * kLog2e : 0.f;
+    }
+    float a = zero, c = -INFINITY, l = 0.f;
+#pragma unroll
+    for (int u = 0; u < PPB; ++u) {
+      join(a, c, val[u], cs[u], lg[u]);
+      l += lg[u];
+    }
+    sa[g][le] = a;
+    sc[g][le] = c;
+    sl[g][le] = l;
+    __syncthreads();
+    float ea = acc, ec = C;  // entering this group
+#pragma unroll
+    for (int k = 0; k < PNG; ++k) {
+      if (k == g) {
+        ea = acc;
+        ec = C;
+      }
+      join(acc, C, sa[k][le], sc[k][le], sl[k][le]);
+    }
+#pragma unroll
+    for (int u = 0; u < PPB; ++u) {
+      if (s0 + u + 1 >= nseg) break;
+      join(ea, ec, val[u], cs[u], lg[u]);
+      pb[(size_t)(s0 + u + 1) * SF + e] = ea;
+    }
+    __syncthreads();  // the groups' sums are read before the next round's
   }
 }
 
@@ -1275,9 +1361,17 @@ hipError_t launch_scan(const void* Q, const void* K, const void* V, const float*
                          dim3(NTH), 0, stream, q, k, v, G, beta, out, ws, H, T, nseg, segc);
     e = hipGetLastError();
     if (e == hipSuccess) {
-      hipLaunchKernelGGL(prefix_kernel<PRIOR>,
-                         dim3((unsigned)((STATE + NTH - 1) / NTH), (unsigned)nbh), dim3(NTH), 0,
-                         stream, ws, ws + (size_t)nbh * nseg * SF, nseg);
+      float* pre = ws + (size_t)nbh * nseg * SF;
+      const dim3 pgrid((unsigned)((STATE + NTH - 1) / NTH), (unsigned)nbh);
+      if (nseg <= kPrefixFew)
+        hipLaunchKernelGGL((prefix_kernel<PRIOR, kPrefixFew - 1>), pgrid, dim3(NTH), 0, stream, ws,
+                           pre, nseg);
+      else if (nseg <= kPrefixOne)
+        hipLaunchKernelGGL((prefix_kernel<PRIOR, kPrefixOne - 1>), pgrid, dim3(NTH), 0, stream, ws,
+                           pre, nseg);
+      else
+        hipLaunchKernelGGL(prefix_wide_kernel<PRIOR>, dim3((unsigned)(STATE / PEN), (unsigned)nbh),
+                           dim3(NTH), 0, stream, ws, pre, nseg);
       e = hipGetLastError();
     }
   }

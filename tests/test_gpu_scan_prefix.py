@@ -1,0 +1,51 @@
+"""Segment prefix of the scans at its batch sizes: 8, 9 and 10 segments, 32 to
+34, over one and two rounds of the split kernel (128 segments each), both
+priors, against the oracle's recurrences on sampled heads.
+
+Tolerance 2e-2 (the bf16 budget), as in the other scan tests.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2602_07160_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+TOL = 2e-2
+
+
+def segments(B, H, T, tile):
+    n = -(-T // tile)
+    c = -(-n // max(1, 512 // (B * H)))
+    return -(-n // c)
+
+
+# (B, H, T, chunk, segments)
+@pytest.mark.parametrize("B,H,T,chunk,nseg", [
+    (1, 64, 500, 64, 8), (1, 56, 570, 64, 9), (1, 51, 640, 64, 10), (1, 16, 2040, 64, 32),
+    (1, 15, 2112, 64, 33), (1, 15, 2150, 64, 34), (1, 4, 8192, 64, 128), (1, 2, 8200, 64, 129),
+    (1, 1, 8320, 32, 260),
+])
+@pytest.mark.parametrize("gla", [False, True])
+def test_segment_counts(fem, B, H, T, chunk, nseg, gla):
+    if gla and chunk != 64:
+        pytest.skip("GLA scans 64-token chunks")
+    assert segments(B, H, T, chunk) == nseg
+    print("[case]", B, H, T, chunk, gla, flush=True)
+    q, k, v, b = inputs.draw(9800 + T + H, B, H, T, 64, beta_lo=0.25, beta_hi=4.0)
+    x = [t.cuda() for t in (q, k, v)]
+    heads = slice(H - 1, H)  # the last head, all rows
+    n = [t[:, heads].double().numpy() for t in (q, k, v)]
+    bn = b[heads].double().numpy()
+    if gla:
+        g = inputs.draw_gla_decay(9900 + T, B, H, T, 64)
+        out = fem.fem_gla_fwd(*x, g.cuda(), b.cuda())
+        want = oracle.fem_gla_recurrent(*n, g[:, heads].double().numpy(), bn)
+    else:
+        out = fem.fem_linear_fwd(*x, b.cuda(), chunk=chunk)
+        want = oracle.fem_linear_recurrent(*n, bn)
+    torch.cuda.synchronize()
+    assert np.abs(out[:, heads].cpu().double().numpy() - want).max() <= TOL
