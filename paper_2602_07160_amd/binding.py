@@ -9,6 +9,7 @@ is raised.
 
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 
@@ -115,9 +116,23 @@ def _workspace(nbytes: int, device, ws, stream):
     return t, t.data_ptr(), nbytes
 
 
+# The current stream's handle without building a torch.cuda.Stream (1.9 us of a
+# ~10 us call), where this torch has the accessor that its own generated code uses.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_HERE = contextlib.nullcontext()
+
+
 def _stream_handle(device, stream) -> int:
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(device.index)
     s = torch.cuda.current_stream(device) if stream is None else stream
     return s.cuda_stream if isinstance(s, torch.cuda.Stream) else int(s)
+
+
+def _on(device):
+    """Context in which ``device`` is current (nothing to do where it already is:
+    entering and leaving torch.cuda.device costs 1.4 us)."""
+    return _HERE if torch.cuda.current_device() == device.index else torch.cuda.device(device)
 
 
 def fem_softmax_fwd(q, k, v, beta, out=None, stream=None) -> torch.Tensor:
@@ -140,7 +155,7 @@ def fem_softmax_fwd(q, k, v, beta, out=None, stream=None) -> torch.Tensor:
     _dev_tensor(out, "out", torch.float32)
     if tuple(out.shape) != (B, H, T, d):
         raise ValueError("out must be [B, H, T, d]")
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         rc = lib.fem_softmax_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
                                  out.data_ptr(), B, H, T, d, FEM_DTYPE[q.dtype],
                                  _stream_handle(q.device, stream))
@@ -174,7 +189,7 @@ def fem_softmax_fwd_ex(q, k, v, beta, out=None, causal: bool = True, out_dtype=t
         raise ValueError("out must be [B, H, T, d_v]")
     flags = (0 if causal else FEM_FLAG_ENCODER) | \
         (FEM_FLAG_OUT_BF16 if out_dtype == torch.bfloat16 else 0)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         rc = lib.fem_softmax_fwd_ex(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
                                     out.data_ptr(), B, H, T, dqk, dv, flags, FEM_DTYPE[q.dtype],
                                     _stream_handle(q.device, stream))
@@ -216,7 +231,7 @@ def fem_softmax_decode_noalloc(q, k_cache, v_cache, beta, lens=None, out=None,
     result as fem_softmax_decode."""
     lib = load()
     B, H, L, dqk, dv, out = _decode_args(q, k_cache, v_cache, beta, lens, out)
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         rc = lib.fem_softmax_decode_noalloc(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
                                             None if lens is None else lens.data_ptr(),
                                             beta.data_ptr(), out.data_ptr(), B, H, L, dqk, dv,
@@ -234,8 +249,8 @@ def fem_softmax_decode(q, k_cache, v_cache, beta, lens=None, out=None, ws=None,
     fp32."""
     lib = load()
     B, H, L, dqk, dv, out = _decode_args(q, k_cache, v_cache, beta, lens, out)
-    need = lib.fem_softmax_decode_workspace_bytes(B, H, L, dqk, dv)
-    with torch.cuda.device(q.device):
+    need = 0 if ws is not None else lib.fem_softmax_decode_workspace_bytes(B, H, L, dqk, dv)
+    with _on(q.device):
         wst, wsp, wsn = _workspace(need, q.device, ws, stream)
         rc = lib.fem_softmax_decode(q.data_ptr(), k_cache.data_ptr(), v_cache.data_ptr(),
                                     None if lens is None else lens.data_ptr(), beta.data_ptr(),
@@ -270,7 +285,7 @@ def fem_softmax_gated_fwd(q, k, v, beta_max, lam, gate=None, out=None, stream=No
     _dev_tensor(out, "out", torch.float32)
     if tuple(out.shape) != (B, H, T, d):
         raise ValueError("out must be [B, H, T, d]")
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         rc = lib.fem_softmax_gated_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(),
                                        beta_max.data_ptr(), lam.data_ptr(),
                                        None if gate is None else gate.data_ptr(),
@@ -304,8 +319,8 @@ def fem_linear_fwd(q, k, v, beta, out=None, chunk: int = 64, ws=None,
     _dev_tensor(out, "out", torch.float32)
     if tuple(out.shape) != (B, H, T, dv):
         raise ValueError("out must be [B, H, T, d_v]")
-    need = lib.fem_linear_workspace_bytes(B, H, T, dk, dv, int(chunk))
-    with torch.cuda.device(q.device):
+    need = 0 if ws is not None else lib.fem_linear_workspace_bytes(B, H, T, dk, dv, int(chunk))
+    with _on(q.device):
         wst, wsp, wsn = _workspace(need, q.device, ws, stream)
         rc = lib.fem_linear_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
                                 out.data_ptr(), B, H, T, dk, dv, int(chunk),
@@ -337,8 +352,8 @@ def fem_gla_fwd(q, k, v, g, beta, out=None, chunk: int = 64, ws=None,
     _dev_tensor(out, "out", torch.float32)
     if tuple(out.shape) != (B, H, T, dv):
         raise ValueError("out must be [B, H, T, d_v]")
-    need = lib.fem_gla_workspace_bytes(B, H, T, dk, dv, int(chunk))
-    with torch.cuda.device(q.device):
+    need = 0 if ws is not None else lib.fem_gla_workspace_bytes(B, H, T, dk, dv, int(chunk))
+    with _on(q.device):
         wst, wsp, wsn = _workspace(need, q.device, ws, stream)
         rc = lib.fem_gla_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), g.data_ptr(),
                              beta.data_ptr(), out.data_ptr(), B, H, T, dk, dv, int(chunk),
@@ -365,7 +380,7 @@ def fem_softmax_fwd_train(q, k, v, beta, out=None, lse=None, stream=None):
     _dev_tensor(lse, "lse", torch.float32)
     if tuple(out.shape) != (B, H, T, d) or tuple(lse.shape) != (B, H, T):
         raise ValueError("out must be [B, H, T, d] and lse [B, H, T]")
-    with torch.cuda.device(q.device):
+    with _on(q.device):
         rc = lib.fem_softmax_fwd_train(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
                                        out.data_ptr(), lse.data_ptr(), B, H, T, d,
                                        FEM_DTYPE[q.dtype], _stream_handle(q.device, stream))
@@ -396,8 +411,8 @@ def fem_softmax_bwd(q, k, v, beta, out, lse, dout, ws=None, stream=None):
     dk = torch.empty_like(dq)
     dv = torch.empty_like(dq)
     db = torch.empty((H, d), device=q.device, dtype=torch.float32)
-    need = lib.fem_softmax_bwd_workspace_bytes(B, H, T, d)
-    with torch.cuda.device(q.device):
+    need = 0 if ws is not None else lib.fem_softmax_bwd_workspace_bytes(B, H, T, d)
+    with _on(q.device):
         wst, wsp, wsn = _workspace(need, q.device, ws, stream)
         rc = lib.fem_softmax_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), beta.data_ptr(),
                                  out.data_ptr(), lse.data_ptr(), dout.data_ptr(), dq.data_ptr(),
