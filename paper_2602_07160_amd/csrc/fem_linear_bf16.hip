@@ -872,10 +872,12 @@ __device__ __forceinline__ void scan_chunk(ScanSmem<PRIOR, CH, NSUB>& sm, f32x16
 // per state entry: S[j][*] carries row shift c_j, z needs none, c is the max.
 // GLA: the state entering segment s+1 is the one entering s, decayed by the
 // total log-decay of segment s along its key channel, plus the own state of s.
-// Latency bounds it, one of loads per batch of PB segments: up to kPrefixFew
-// segments take one batch of 8, up to kPrefixOne one of 32 (GLA, 20 segments
+// Latency bounds it.  Up to kPrefixFew segments take one batch of PB = 8 and
+// the linear prior goes on in batches of 8 up to kPrefixOne (PB = 32 gained it
+// nothing: B5 H8 T3000, 12 segments, 45.3 and 45.6 us a call); GLA, whose
+// decays lengthen the chain between batches, takes one batch of 32 (20 segments
 // of 24 (b, h): 11.7 us in batches of 8, 8.1 so, 32 in prefix_wide_kernel, most
-// of whose groups would be idle); prefix_wide_kernel takes more.
+// of whose groups would be idle).  prefix_wide_kernel takes more.
 constexpr int kPrefixFew = 9, kPrefixOne = 33;
 template <int PRIOR, int PB>
 __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ own,
@@ -896,7 +898,9 @@ __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ o
     float val[PB], cs[PB], lg[PB];
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
-      const size_t o = (size_t)min(s0 + u, nseg - 2) * SF;  // (past the end: unused)
+      val[u] = cs[u] = lg[u] = 0.f;
+      if (s0 + u + 1 >= nseg) continue;  // the same for every thread
+      const size_t o = (size_t)(s0 + u) * SF;
       val[u] = ob[o + e];
       cs[u] = j >= 0 ? ob[o + DV * DK + DK + j] : 0.f;
       lg[u] = (PRIOR == kGla && kc >= 0) ? ob[o + STATE + kc] : 0.f;
@@ -1363,7 +1367,7 @@ hipError_t launch_scan(const void* Q, const void* K, const void* V, const float*
     if (e == hipSuccess) {
       float* pre = ws + (size_t)nbh * nseg * SF;
       const dim3 pgrid((unsigned)((STATE + NTH - 1) / NTH), (unsigned)nbh);
-      if (nseg <= kPrefixFew)
+      if (nseg <= (PRIOR == kGla ? kPrefixFew : kPrefixOne))
         hipLaunchKernelGGL((prefix_kernel<PRIOR, kPrefixFew - 1>), pgrid, dim3(NTH), 0, stream, ws,
                            pre, nseg);
       else if (nseg <= kPrefixOne)
