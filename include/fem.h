@@ -84,7 +84,7 @@ typedef enum {
  *   beta    : [H, d] float32, > 0
  *   out     : [B, H, T, d] float32
  *   d       : 32, 64 or 128 for FEM_DTYPE_BF16 (matrix-core path);
- *             any 1 <= d <= 256 for FEM_DTYPE_F32 (exact vector path)
+ *             any 1 <= d <= 256 for FEM_DTYPE_F32 (fp32 matrix path)
  *
  * Score scale is fixed at 1/sqrt(d).  Returns a fem_status.
  */
