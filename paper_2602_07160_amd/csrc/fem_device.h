@@ -72,58 +72,7 @@ __device__ __forceinline__ unsigned lds_addr(const void* p) {
 // it, so the block saves m0 into a scratch SGPR and restores it after the
 // load has issued (the load reads m0 at issue): whatever the compiler keeps
 // in m0 survives the block.
-__device__ __forceinline__ void dma16(const void* src, void* dst) {
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %2\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(src), "s"(__builtin_amdgcn_readfirstlane(lds_addr(dst)))
-      : "memory");
-}
-// The same load with a wave-uniform 64-bit base in SGPRs and a 32-bit lane
-// offset: one VGPR per load instead of a 64-bit address pair.  The base is
-// the same in every lane; it is read from the first lane so that it sits in
-// SGPRs wherever the compiler cannot prove it uniform.
-__device__ __forceinline__ void dma16s(const void* base_any, unsigned off, void* dst) {
-  // (the builtin returns int: each half is widened as unsigned, never sign-extended)
-  const uint64_t b = reinterpret_cast<uint64_t>(base_any);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)b);
-  const uint64_t base = ((uint64_t)hi << 32) | (uint64_t)lo;
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds_addr(dst)))
-      : "memory");
-}
-// The same load with the LDS byte address given as an integer the caller
-// keeps wave-uniform (no pointer conversion per load): with a uniform base
-// and address the block is five scalar instructions and the load.
-__device__ __forceinline__ void dma16u(const void* base_any, unsigned off, unsigned lds) {
-  const uint64_t b = reinterpret_cast<uint64_t>(base_any);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
-  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)b);
-  const uint64_t base = ((uint64_t)hi << 32) | (uint64_t)lo;
-  unsigned saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %3\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dwordx4 %1, %2\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "v"(off), "s"(base), "s"((unsigned)__builtin_amdgcn_readfirstlane(lds))
-      : "memory");
-}
+//
 // Buffer-resource form: rsrc covers [base, base + bytes) (a raw buffer:
 // stride 0, 32-bit data format), so a lane whose offset falls past its end
 // loads zeros and reads nothing outside the range.  All operands wave-uniform
