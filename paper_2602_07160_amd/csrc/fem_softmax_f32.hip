@@ -60,12 +60,18 @@ __device__ __forceinline__ f32x16 mfma32(float a, float b, const f32x16& c) {
 // Accumulator row of register i in lane half hl.
 __device__ __forceinline__ int acc_row(int i, int hl) { return 8 * (i >> 2) + 4 * hl + (i & 3); }
 
+// base and bytes are wave-uniform; read from the first lane, they sit in SGPRs
+// also where the compiler formed them on the vector unit.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf(const float* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), (short)0, (int)bytes,
+  const uint64_t b = reinterpret_cast<uint64_t>(base);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(b >> 32));
+  const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((unsigned)b);
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<float*>(((uint64_t)hi << 32) | lo),
+                                           (short)0, __builtin_amdgcn_readfirstlane((int)bytes),
                                            0x00020000);
 }
-__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, unsigned off, int soff) {
-  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, soff, 0));
+__device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, unsigned off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
 // Exact fp32 read of channels ch[0..nb) of row t by one wave: per channel the
@@ -132,10 +138,11 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
   float* Oh = out + base;
   const float scale2 = kLog2e / sqrtf((float)d);
 
-  // Rows t0 .. t0 + 31 of a [T, d] matrix as a buffer resource: one 32-bit
-  // lane offset serves every load of a tile, and rows at or past T read zero.
-  const auto rows = [&](const float* x, int t0) {
-    return buf(x + (size_t)t0 * d, (unsigned)min(kRows, T - t0) * (unsigned)d * 4u);
+  // Rows t0 + r0 .. t0 + 31 of a [T, d] matrix as a buffer resource: one 32-bit
+  // lane offset serves every load, and rows at or past T read zero.
+  const auto rows = [&](const float* x, int t0, int r0) {
+    return buf(x + (size_t)(t0 + r0) * d,
+               (unsigned)max(min(kRows, T - t0) - r0, 0) * (unsigned)d * 4u);
   };
   // dims 8g + 4hl + 0..3 of row n of a tile.  Dims at or past d read whatever
   // follows (the query holds zeros there).
@@ -144,7 +151,7 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
     f32x4 x;
     if constexpr (FORM == kAny) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = load1(r, koff + (8 * g + u) * 4u, 0);
+      for (int u = 0; u < 4; ++u) x[u] = load1(r, koff + (8 * g + u) * 4u);
     } else {
       x = __builtin_bit_cast(
           f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, (int)(koff + 32u * g), 0, 0));
@@ -167,7 +174,7 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
     const int q0 = qb * kRows, tq = q0 + n;
     f32x4 qf[NG];
     {
-      const __amdgpu_buffer_rsrc_t rq = rows(Qh, q0);
+      const __amdgpu_buffer_rsrc_t rq = rows(Qh, q0, 0);
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
         qf[g] = load4(rq, g);
@@ -178,11 +185,20 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
         }
       }
     }
-    // V of this lane's channel cb * 32 + n, keys acc_row(i, hl) of the tile
-    const auto load_v = [&](__amdgpu_buffer_rsrc_t r, int cb, f32x16& x) {
-      const unsigned off = (unsigned)(4 * hl * d + ch[cb]) * 4u;
+    // V of this lane's channel cb * 32 + n, keys acc_row(i, hl) of tile t0.  The
+    // row steps of 8 are resources of their own, so that every load's bounds
+    // check sees its whole offset (a scalar offset is not part of that check).
+    // The lane offset is formed anew for every block: kept for all of them,
+    // the wide forms spill it (d = 128 256 bytes a lane, 212 so).
+    const auto load_v = [&](int t0, int cb, f32x16& x) {
+      unsigned off = (unsigned)(4 * hl * d + ch[cb]) * 4u;
+      asm volatile("" : "+v"(off));
 #pragma unroll
-      for (int i = 0; i < 16; ++i) x[i] = load1(r, off, (8 * (i >> 2) + (i & 3)) * d * 4);
+      for (int g = 0; g < 4; ++g) {
+        const __amdgpu_buffer_rsrc_t r = rows(Vh, t0, 8 * g);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[4 * g + u] = load1(r, off + (unsigned)(u * d) * 4u);
+      }
     };
 
     f32x16 acc[NCB], vx[NVB];
@@ -198,11 +214,10 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
       cj[cb] = -INFINITY;
     }
     if (wave <= qb) {
-      const __amdgpu_buffer_rsrc_t rk = rows(Kh, wave * kRows), rv = rows(Vh, wave * kRows);
-      load_kc(rk, 0);
+      load_kc(rows(Kh, wave * kRows, 0), 0);
       if (AHEAD) {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) load_v(rv, cb, vx[cb]);
+        for (int cb = 0; cb < NCB; ++cb) load_v(wave * kRows, cb, vx[cb]);
       }
     }
     // One tile; last: the diagonal one, with the causal mask and, where T ends
@@ -210,10 +225,9 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
     const auto tile = [&](const int kb, const auto last) __attribute__((always_inline)) {
       const int k0 = kb * kRows;
       const int kn = min(kb + kWaves, qb) * kRows;  // (past the end: loaded, not used)
-      // resources of the loads below: K of this tile's later chunks, V of
-      // this tile (wide) or the next, K of the next tile
-      const __amdgpu_buffer_rsrc_t rk = rows(Kh, k0), rv = rows(Vh, AHEAD ? kn : k0),
-                                   rkn = rows(Kh, kn);
+      // resources of the loads below: K of this tile's later chunks and of the
+      // next tile
+      const __amdgpu_buffer_rsrc_t rk = rows(Kh, k0, 0), rkn = rows(Kh, kn, 0);
       // ---- tilt of block cb: column maximum, lazily raised shift, E in place
       // of V; the shift's factor is owed to the accumulator
       float owed[NCB];
@@ -244,7 +258,7 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         if (c + 1 < NC) load_kc(rk, c + 1);
-        else if (!AHEAD) load_v(rv, 0, vx[0]);
+        else if (!AHEAD) load_v(k0, 0, vx[0]);
 #pragma unroll
         for (int g = 0; g < KC; ++g)
 #pragma unroll
@@ -295,14 +309,14 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
         if (!AHEAD) {
-          if (cb + 1 < NCB) load_v(rv, cb + 1, vx[(cb + 1) % NVB]);
+          if (cb + 1 < NCB) load_v(k0, cb + 1, vx[(cb + 1) % NVB]);
           else load_kc(rkn, 0);
           tilt(cb);
         }
         pay(cb);
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[cb] = mfma32(vx[cb % NVB][i], s[i], acc[cb]);
-        if (AHEAD) load_v(rv, cb, vx[cb]);
+        if (AHEAD) load_v(kn, cb, vx[cb]);
         else __builtin_amdgcn_sched_barrier(0);
       }
     };

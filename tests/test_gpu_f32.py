@@ -57,3 +57,11 @@ def test_nan_value_reaches_its_rows_only(fem):
     assert np.isnan(got[0, 0, 70:, 5]).all()
     got[0, 0, 70:, 5] = want[0, 0, 70:, 5]
     assert np.abs(got - want).max() <= TOL
+
+
+# a second tile per wave at the widths whose loads take the narrow forms
+@pytest.mark.parametrize("T", [160, 257])
+@pytest.mark.parametrize("d", [33, 70, 101, 132, 200, 255])
+def test_ragged_widths(fem, T, d):
+    x = inputs.draw(9650 + 300 * T + d, 1, 2, T, d, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+    assert np.abs(read(fem, *x) - ref(*x)).max() <= TOL
