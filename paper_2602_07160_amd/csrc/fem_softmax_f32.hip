@@ -12,8 +12,9 @@
 // with m_t a running row maximum and c_j a running column maximum, both raised
 // lazily.  The exponents carry no bias: near the maxima they are small, so
 // their rounding stays at 2^-24 of the term.  An output whose weighted mean
-// of E fell below kLow (or is NaN) may have lost terms to underflow; it is
-// recomputed from its own keys by a joint log-sum-exp per (t, j).
+// of E fell below kLow may have lost terms to underflow; it, and one whose
+// mean passed kHigh or is NaN, is recomputed from its own keys by a joint
+// log-sum-exp per (t, j).
 //
 // Bound by the fp32 matrix rate (64 cycles per 32x32x2 product, 155 TFLOP/s
 // as measured on a large product).  One workgroup takes 32 query rows; its
@@ -48,6 +49,10 @@ constexpr float kColLag = 16.f;
 // Smallest trusted O / l.  A term that P or E flushed to zero was below 2^-126
 // times 2^kColLag, so 2^24 keys lose less than 2^-86, 2^-24 of 2^-62.
 constexpr float kLow = 0x1p-60f;
+// Largest trusted O / l.  It stays near 2^kColLag as long as the exponents do;
+// only where the rounding of c_j itself (2^-24 of |beta v|) is of that size,
+// from |beta v| of about 2^30 on, can E pass it, up to infinity.
+constexpr float kHigh = 0x1p60f;
 constexpr int kBatch = 8;         // channels recomputed per pass of the exact path
 
 // How the widths meet: d == D; d a multiple of 4 below D; any d below D.
@@ -385,7 +390,7 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
         const float mean = ((sm.o[0][at] + sm.o[1][at]) + (sm.o[2][at] + sm.o[3][at])) / L;
         const bool live = on && t < T;
         if (live) Oh[(size_t)t * d + j] = (log2_hw(mean) + C) * ib;
-        low |= live && !(mean >= kLow) ? 1u << p : 0u;
+        low |= live && !(mean >= kLow && mean <= kHigh) ? 1u << p : 0u;
       }
       // rare: a mean that lost range (or is NaN), recomputed exactly, one row
       // at a time by the whole wave

@@ -65,3 +65,17 @@ def test_nan_value_reaches_its_rows_only(fem):
 def test_ragged_widths(fem, T, d):
     x = inputs.draw(9650 + 300 * T + d, 1, 2, T, d, dtype="f32", beta_lo=0.25, beta_hi=4.0)
     assert np.abs(read(fem, *x) - ref(*x)).max() <= TOL
+
+
+# From |beta v| of about 2^30 on, the rounding of the shift beta max(v) alone
+# passes the exponent's range.  Relative to the column's largest value: 2^-20
+# (a few roundings of the exponents and of the result).
+@pytest.mark.parametrize("size", [1e9, 1e10, 1e30])
+@pytest.mark.parametrize("T,d", [(32, 32), (100, 64), (300, 20), (200, 128)])
+def test_large_values(fem, T, d, size):
+    q, k, v, b = inputs.draw(9700 + T, 1, 2, T, d, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+    v[:, :, :, : d // 2] *= size
+    v[:, :, :, d // 2] = -size  # a column that holds a mask value
+    got, want = read(fem, q, k, v, b), ref(q, k, v, b)
+    scale = np.maximum(1.0, np.abs(v.double().numpy()).max(2, keepdims=True))
+    assert (np.abs(got - want) / scale).max() <= 2.0 ** -20
