@@ -79,6 +79,29 @@ __device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
+// Streaming log2-sum-exp2 accumulator: value = m + log2(s), for
+// terms of any kind: a term of -inf adds
+// nothing, +inf gives +inf, and NaN stays in s whatever m is.
+struct LseAny {
+  float m = -INFINITY;
+  float s = 0.f;
+  __device__ __forceinline__ void add(float w) {
+    if (w > m) {
+      s = s * exp2_hw(m - w) + 1.f;
+      m = w;
+    } else if (w != -INFINITY) {
+      s += w == m ? 1.f : exp2_hw(w - m);
+    }
+  }
+  // Combine across the 64 lanes of a wave; every lane gets the total.
+  __device__ __forceinline__ float wave_total() const {
+    float M = wave_max(m);
+    float part = s == 0.f ? 0.f : m == M ? s : s * exp2_hw(m - M);
+    float S = wave_sum(part);
+    return M + log2_hw(S);
+  }
+};
+
 // Exact fp32 read of channels ch[0..nb) of row t by one wave: per channel the
 // joint log-sum-exp of (score + tilt) over the keys i <= t, minus that of
 // the scores.  Lane c < nb returns channel ch[c]'s value.
@@ -86,7 +109,7 @@ __device__ float exact_row_f32(const float* __restrict__ Qh, const float* __rest
                                const float* __restrict__ Vh, int t, int d, const int (&ch)[kBatch],
                                const float (&bl)[kBatch], int nb, float scale2) {
   const int lane = threadIdx.x & 63;
-  Lse2 den, num[kBatch];
+  LseAny den, num[kBatch];
   const float* qr = Qh + (size_t)t * d;
   for (int i = lane; i <= t; i += 64) {
     const float* kr = Kh + (size_t)i * d;

@@ -79,3 +79,34 @@ def test_large_values(fem, T, d, size):
     got, want = read(fem, q, k, v, b), ref(q, k, v, b)
     scale = np.maximum(1.0, np.abs(v.double().numpy()).max(2, keepdims=True))
     assert (np.abs(got - want) / scale).max() <= 2.0 ** -20
+
+
+@pytest.mark.parametrize("key", [0, 10, 70])
+@pytest.mark.parametrize("where", ["k", "v"])
+def test_nan_reaches_every_row_that_sees_it(fem, where, key):
+    q, k, v, b = inputs.draw(9750, 1, 1, 150, 64, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+    want = ref(q, k, v, b)
+    ch = slice(None) if where == "k" else slice(5, 6)
+    (k if where == "k" else v)[0, 0, key, 5] = float("nan")
+    got = read(fem, q, k, v, b)
+    assert np.isnan(got[0, 0, key:, ch]).all()
+    got[0, 0, key:, ch] = want[0, 0, key:, ch]
+    assert np.abs(got - want).max() <= TOL
+
+
+def test_infinite_and_lowest_values(fem):
+    """+inf in V gives +inf to the rows that see it; the type's lowest value
+    (a mask) has no weight, also where it fills a tile or a lane's first keys."""
+    q, k, v, b = inputs.draw(9760, 1, 1, 150, 64, dtype="f32", beta_lo=1.0, beta_hi=4.0)
+    low = torch.finfo(torch.float32).min
+    v[0, 0, 20, 1] = float("inf")
+    v[0, 0, 1:10, 2] = low
+    v[0, 0, 32:96, 3] = low
+    v[0, 0, 1:140, 4] = low
+    got = read(fem, q, k, v, b)
+    w = v.clone()
+    w[0, 0, 20, 1] = 0.0
+    want = ref(q, k, w, b)
+    assert np.isposinf(got[0, 0, 20:, 1]).all()
+    got[0, 0, 20:, 1] = want[0, 0, 20:, 1]
+    assert np.abs(got - want).max() <= TOL
