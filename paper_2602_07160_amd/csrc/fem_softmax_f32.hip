@@ -29,9 +29,13 @@
 // The next tile's K loads are issued after the last product that reads the
 // current ones and its V loads after O's, one tile ahead of their use.
 // B4 H12 T1024 d64: 3950 us with one workgroup per query row on the vector
-// units, 79 us here (82 TFLOP/s; 113 at B2 H24 T4096, where a workgroup's
-// start and end weigh less); B1 H1 T128 d32: 28 and 5.7 us.  Error against
-// float64 at these shapes 2e-7 to 3e-7 of the 2-norm (5e-7 to 1.2e-6 before).
+// units, 77 us here (83 TFLOP/s; 112 at B2 H24 T4096, where a workgroup's
+// start and end weigh less); B1 H1 T128 d32: 28 and 5.7 us.  Other widths at
+// T1024: B4 H12 d32 3810 and 40, d50 3890 and 107; B2 H12 d96 2310
+// and 93, d128 2370 and 86; B1 H12 d130 1350 and 146, d200 1415 and 174, d256
+// 1495 and 117 (a width that is no multiple of four loads K one dword at a
+// time).  Error against float64 at these shapes 2e-7 to 3e-7 of the 2-norm
+// (5e-7 to 1.2e-6 before).
 
 #include "fem_device.h"
 #include "fem_internal.h"
@@ -53,7 +57,6 @@ constexpr float kLow = 0x1p-60f;
 // only where the rounding of c_j itself (2^-24 of |beta v|) is of that size,
 // from |beta v| of about 2^30 on, can E pass it, up to infinity.
 constexpr float kHigh = 0x1p60f;
-constexpr int kBatch = 8;         // channels recomputed per pass of the exact path
 
 // How the widths meet: d == D; d a multiple of 4 below D; any d below D.
 constexpr int kFull = 0, kVec4 = 1, kAny = 2;
@@ -79,60 +82,6 @@ __device__ __forceinline__ float load1(__amdgpu_buffer_rsrc_t r, unsigned off) {
   return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
 }
 
-// Streaming log2-sum-exp2 accumulator: value = m + log2(s), for
-// terms of any kind: a term of -inf adds
-// nothing, +inf gives +inf, and NaN stays in s whatever m is.
-struct LseAny {
-  float m = -INFINITY;
-  float s = 0.f;
-  __device__ __forceinline__ void add(float w) {
-    if (w > m) {
-      s = s * exp2_hw(m - w) + 1.f;
-      m = w;
-    } else if (w != -INFINITY) {
-      s += w == m ? 1.f : exp2_hw(w - m);
-    }
-  }
-  // Combine across the 64 lanes of a wave; every lane gets the total.
-  __device__ __forceinline__ float wave_total() const {
-    float M = wave_max(m);
-    float part = s == 0.f ? 0.f : m == M ? s : s * exp2_hw(m - M);
-    float S = wave_sum(part);
-    return M + log2_hw(S);
-  }
-};
-
-// Exact fp32 read of channels ch[0..nb) of row t by one wave: per channel the
-// joint log-sum-exp of (score + tilt) over the keys i <= t, minus that of
-// the scores.  Lane c < nb returns channel ch[c]'s value.
-__device__ float exact_row_f32(const float* __restrict__ Qh, const float* __restrict__ Kh,
-                               const float* __restrict__ Vh, int t, int d, const int (&ch)[kBatch],
-                               const float (&bl)[kBatch], int nb, float scale2) {
-  const int lane = threadIdx.x & 63;
-  LseAny den, num[kBatch];
-  const float* qr = Qh + (size_t)t * d;
-  for (int i = lane; i <= t; i += 64) {
-    const float* kr = Kh + (size_t)i * d;
-    float dot = 0.f;
-    for (int c = 0; c < d; ++c) dot = fmaf(qr[c], kr[c], dot);
-    const float s = dot * scale2;
-    den.add(s);
-#pragma unroll
-    for (int c = 0; c < kBatch; ++c)
-      if (c < nb) num[c].add(fmaf(Vh[(size_t)i * d + ch[c]], bl[c], s));
-  }
-  const float l = den.wave_total();
-  float mine = 0.f;
-#pragma unroll
-  for (int c = 0; c < kBatch; ++c) {
-    if (c < nb) {
-      const float o = (num[c].wave_total() - l) / bl[c];
-      if (lane == c) mine = o;
-    }
-  }
-  return mine;
-}
-
 template <int D>
 struct F32Smem {
   static constexpr int OROW = D + 1;
@@ -140,10 +89,205 @@ struct F32Smem {
   float m[kWaves][kRows], l[kWaves][kRows];
   __align__(16) float f[kWaves][D];  // column factors to the common shift
   float c[kWaves][D], bl[D];         // column shifts; beta log2 e
+  __align__(16) int redo[kWaves];      // per wave: has outputs to recompute
 };
 
+// How the epilogue and the recomputation share out a block's outputs: thread
+// tid has channel j0 + tid % kLanes of each group of kLanes channels, and rows
+// p * kStep + tid / kLanes, p < kPasses.
+template <int D>
+struct Share {
+  static constexpr int kLanes = D < 64 ? D : 64;
+  static constexpr int kStep = kWaves * 64 / kLanes;
+  static constexpr int kPasses = kRows / kStep;
+  static constexpr int kGroups = D / kLanes;
+  static_assert(kGroups * kPasses <= 32, "one flag word per thread");
+};
+
+// x with -inf and +inf replaced by the type's largest values.
+__device__ __forceinline__ float finite(float x) {
+  return __builtin_amdgcn_fmed3f(x, -3.4028235e38f, 3.4028235e38f);
+}
+
+// (M, S) of a log2-sum-exp2 M + log2(S), and N further terms.  M may be any
+// value: a term of -inf adds nothing, +inf gives +inf and NaN stays in S.
+template <int N>  // a power of two
+__device__ __forceinline__ void lse_add(float& M, float& S, const float (&x)[N]) {
+  float mx = M;
+#pragma unroll
+  for (int u = 0; u < N; ++u) mx = fmaxf(mx, x[u]);
+  const float at = finite(mx);
+  float e[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) e[u] = exp2_hw(x[u] - at);
+#pragma unroll
+  for (int w = N / 2; w > 0; w >>= 1) {
+#pragma unroll
+    for (int u = 0; u < w; ++u) e[u] += e[u + w];
+  }
+  S = fmaf(S, exp2_hw(M - at), e[0]);
+  M = mx;
+}
+
+// The flagged outputs of one block (bit group * kPasses + p of `low`: this
+// thread's row of pass p) from their own keys: F = (LSE_i(s_i + beta v_i) - LSE_i(s_i)) / beta, each
+// log-sum-exp with its own maximum, i.e. without shared shifts.  Per round the
+// four waves form the scores of four key tiles on the matrix instructions,
+// leave them in LDS, and each thread then takes them through the sums of its
+// channels and rows that have a flagged output, eight keys at a time with V
+// read once for all its rows.  Dims at or past d are zero in both operands (in
+// the block's first pass K holds the next row's there).
+// Bound by the exponentials.  Every output flagged (us a call; then a wave
+// taking one row and eight channels at a time, which formed the row's scores
+// anew for each; then the first kernel, one workgroup a row): B4 H12 T1024 d64
+// 213, 3085 and 3980; B2 H12 T1024 d128 384, 9370 and 2440; B1 H12 T1024 d256
+// 714, 32100 and 1580.  Only where four blocks a head leave the chip idle is
+// the first one ahead: B1 H2 T128 d64 36, 600 and 32, d256 120, 4660 and 37.
+template <int D, int FORM, class Rows, class Load4>
+__device__ __forceinline__ void recompute(F32Smem<D>& sm, Rows&& rows, Load4&& load4,
+                                          const float* __restrict__ Qh,
+                                          const float* __restrict__ Kh,
+                                          const float* __restrict__ Vh, float* __restrict__ Oh,
+                                          int T, int d, int qb, unsigned low, float scale2) {
+  using Sh = Share<D>;
+  constexpr int NP = Sh::kPasses, NG = Sh::kGroups, KU = 8, SROW = kWaves * kRows + 4;
+  static_assert(kRows * SROW * sizeof(float) <= sizeof(sm.o), "the scores take O's place");
+  float* sc = &sm.o[0][0];  // [query][key of the round]
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // nothing of this is formed, and held, before the tile loop
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 31, hl = lane >> 5, q0 = qb * kRows;
+  const __amdgpu_buffer_rsrc_t rq = rows(Qh, q0, 0);
+  const auto frag = [&](__amdgpu_buffer_rsrc_t r, int g) {
+    f32x4 x = load4(r, g);
+    if constexpr (FORM != kFull) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (8 * g + 4 * hl + u >= d) x[u] = 0.f;
+    }
+    return x;
+  };
+  const int r0 = tid / Sh::kLanes;
+  int ch[NG];
+  float bl[NG], M[NG][NP], S[NG][NP], m = -INFINITY, l = 0.f;
+  unsigned rowsof = 0;  // bits as in low: some lane of this wave has a flagged output
+#pragma unroll
+  for (int group = 0; group < NG; ++group) {
+    const int j = group * Sh::kLanes + tid % Sh::kLanes;
+    ch[group] = min(j, d - 1);
+    bl[group] = sm.bl[j];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      const int bit = group * NP + p;
+      rowsof |= __any((low >> bit) & 1u) ? 1u << bit : 0u;
+      M[group][p] = -INFINITY;
+      S[group][p] = 0.f;
+    }
+  }
+  for (int kb0 = 0; kb0 <= qb; kb0 += kWaves) {
+    const int kb = kb0 + wave, k0 = kb0 * kRows;
+    if (kb <= qb) {
+      const __amdgpu_buffer_rsrc_t rk = rows(Kh, kb * kRows, 0);
+      f32x16 s = {};
+#pragma unroll 4
+      for (int g = 0; g < D / 8; ++g) {
+        const f32x4 a = frag(rk, g), b = frag(rq, g);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s = mfma32(a[u], b[u], s);
+      }
+      float x[16];
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        x[i] = kb * kRows + acc_row(i, hl) > q0 + n ? -INFINITY : s[i] * scale2;
+      lse_add(m, l, x);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4*>(sc + n * SROW + wave * kRows + 8 * g + 4 * hl) =
+            f32x4{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+    }
+    __syncthreads();
+    const int nk = min(kWaves, qb + 1 - kb0) * kRows;
+    // last: the round of the diagonal tile (keys after a row stay out, whatever V holds)
+    const auto walk = [&](const auto group, const auto last) __attribute__((always_inline)) {
+      constexpr int G = decltype(group)::value;
+      const float* vj = Vh + ch[G];
+      const auto load_v = [&](int kk, float (&v)[KU]) {
+#pragma unroll
+        for (int u = 0; u < KU; ++u) v[u] = vj[(size_t)min(k0 + kk + u, T - 1) * d];
+      };
+      float v[KU], vn[KU];
+      load_v(0, v);
+      for (int kk = 0; kk < nk; kk += KU) {
+        load_v(kk + KU, vn);
+        f32x4 sr[NP][KU / 4];  // every row's scores first: one wait
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+          for (int w = 0; w < KU / 4; ++w)
+            sr[p][w] = *reinterpret_cast<const f32x4*>(sc + (p * Sh::kStep + r0) * SROW + kk + 4 * w);
+#pragma unroll
+        for (int p0 = 0; p0 < NP; p0 += 2) {  // rows in pairs: two independent chains
+          if (!((rowsof >> (G * NP + p0)) & 3u)) continue;
+#pragma unroll
+          for (int p = p0; p < p0 + 2; ++p) {
+            const int lim = q0 + p * Sh::kStep + r0 - (k0 + kk);
+            float x[KU];
+#pragma unroll
+            for (int u = 0; u < KU; ++u) {
+              x[u] = fmaf(v[u], bl[G], sr[p][u >> 2][u & 3]);
+              if (decltype(last)::value && u > lim) x[u] = -INFINITY;
+            }
+            lse_add(M[G][p], S[G][p], x);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < KU; ++u) v[u] = vn[u];
+      }
+    };
+    const auto walk_group = [&](const auto group) __attribute__((always_inline)) {
+      if (!((rowsof >> (decltype(group)::value * NP)) & ((1u << NP) - 1u))) return;
+      if (kb0 + kWaves > qb) walk(group, std::true_type());
+      else walk(group, std::false_type());
+    };
+    walk_group(std::integral_constant<int, 0>());
+    if constexpr (NG > 1) walk_group(std::integral_constant<int, 1>());
+    if constexpr (NG > 2) {
+      walk_group(std::integral_constant<int, 2>());
+      walk_group(std::integral_constant<int, 3>());
+    }
+    __syncthreads();  // the scores are read before the next round's
+  }
+  // the scores' log-sum-exp: lane halves, then the waves' parts
+  {
+    const float m1 = other_half(m), l1 = other_half(l), mx = fmaxf(m, m1), at = finite(mx);
+    l = l * exp2_hw(m - at) + l1 * exp2_hw(m1 - at);
+    if (hl == 0) {
+      sm.m[wave][n] = mx;
+      sm.l[wave][n] = l;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < NP; ++p) {
+    const int r = p * Sh::kStep + r0;
+    float mr = sm.m[0][r];
+#pragma unroll
+    for (int w = 1; w < kWaves; ++w) mr = fmaxf(mr, sm.m[w][r]);
+    const float at = finite(mr);
+    float lr = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) lr += sm.l[w][r] * exp2_hw(sm.m[w][r] - at);
+#pragma unroll
+    for (int group = 0; group < NG; ++group)
+      if ((low >> (group * NP + p)) & 1u)
+        Oh[(size_t)(q0 + r) * d + ch[group]] =
+            ((M[group][p] - mr) + (log2_hw(S[group][p]) - log2_hw(lr))) / bl[group];
+  }
+  __syncthreads();  // the tables are read before the next block's
+}
+
 template <int D, int FORM>
-__global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_kernel(
+__global__ __launch_bounds__(kWaves * 64, D <= 32 ? 3 : D <= 128 ? 2 : 1) void softmax_f32_kernel(
     const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
     const float* __restrict__ beta, float* __restrict__ out, int H, int T, int d_arg, int nqb) {
   constexpr int NCB = D / 32;       // 32-channel blocks
@@ -169,8 +313,9 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
   // Rows t0 + r0 .. t0 + 31 of a [T, d] matrix as a buffer resource: one 32-bit
   // lane offset serves every load, and rows at or past T read zero.
   const auto rows = [&](const float* x, int t0, int r0) {
-    return buf(x + (size_t)(t0 + r0) * d,
-               (unsigned)max(min(kRows, T - t0) - r0, 0) * (unsigned)d * 4u);
+    const int end = min(kRows, T - t0);
+    // (a select, not max: min and max together become one vector instruction)
+    return buf(x + (size_t)(t0 + r0) * d, (unsigned)(end > r0 ? end - r0 : 0) * (unsigned)d * 4u);
   };
   // dims 8g + 4hl + 0..3 of row n of a tile.  Dims at or past d read whatever
   // follows (the query holds zeros there).
@@ -214,18 +359,21 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
       }
     }
     // V of this lane's channel cb * 32 + n, keys acc_row(i, hl) of tile t0.  The
-    // row steps of 8 are resources of their own, so that every load's bounds
-    // check sees its whole offset (a scalar offset is not part of that check).
-    // The lane offset is formed anew for every block: kept for all of them,
-    // the wide forms spill it (d = 128 256 bytes a lane, 212 so).
+    // row steps beyond the immediate offset's 4 KiB (steps of 8 for a runtime
+    // d) are resources of their own, so that every load's bounds check sees its
+    // whole offset (a scalar offset is not part of that check).  vrow, the
+    // lane's first row, passes through every tile unseen: as a loop invariant
+    // its sums with the steps would each take a register, and spill.
+    unsigned vrow = (unsigned)(4 * hl * d + (FORM == kFull ? n : 0)) * 4u;
     const auto load_v = [&](int t0, int cb, f32x16& x) {
-      unsigned off = (unsigned)(4 * hl * d + ch[cb]) * 4u;
-      asm volatile("" : "+v"(off));
+      constexpr int GR = FORM != kFull ? 1 : D == 32 ? 4 : D == 64 ? 2 : 1;  // steps a resource
+      const unsigned off = vrow + (unsigned)(FORM == kFull ? cb * 32 : ch[cb]) * 4u;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
+      for (int g = 0; g < 4; g += GR) {
         const __amdgpu_buffer_rsrc_t r = rows(Vh, t0, 8 * g);
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[4 * g + u] = load1(r, off + (unsigned)(u * d) * 4u);
+        for (int i = 0; i < 4 * GR; ++i)
+          x[4 * g + i] = load1(r, off + (unsigned)((8 * (i >> 2) + (i & 3)) * d) * 4u);
       }
     };
 
@@ -241,11 +389,16 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
       acc[cb] = f32x16{};
       cj[cb] = -INFINITY;
     }
-    if (wave <= qb) {
-      load_kc(rows(Kh, wave * kRows, 0), 0);
+    // K before V, as in the tile loop, and without a branch around them (a wave
+    // without a tile loads the last one and drops it): the loop's first wait is
+    // shared by every way into it, and would otherwise be for V too.
+    {
+      const int kf0 = min(wave, qb) * kRows;
+      load_kc(rows(Kh, kf0, 0), 0);
+      __builtin_amdgcn_sched_barrier(0);
       if (AHEAD) {
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) load_v(wave * kRows, cb, vx[cb]);
+        for (int cb = 0; cb < NCB; ++cb) load_v(kf0, cb, vx[cb]);
       }
     }
     // One tile; last: the diagonal one, with the causal mask and, where T ends
@@ -253,6 +406,7 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
     const auto tile = [&](const int kb, const auto last) __attribute__((always_inline)) {
       const int k0 = kb * kRows;
       const int kn = min(kb + kWaves, qb) * kRows;  // (past the end: loaded, not used)
+      asm("" : "+v"(vrow));
       // resources of the loads below: K of this tile's later chunks and of the
       // next tile
       const __amdgpu_buffer_rsrc_t rk = rows(Kh, k0, 0), rkn = rows(Kh, kn, 0);
@@ -344,8 +498,17 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
         pay(cb);
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[cb] = mfma32(vx[cb % NVB][i], s[i], acc[cb]);
-        if (AHEAD) load_v(kn, cb, vx[cb]);
-        else __builtin_amdgcn_sched_barrier(0);
+        if (AHEAD) {
+          load_v(kn, cb, vx[cb]);
+          // exponentials, products and loads in turn (left alone, the loads
+          // come in one burst after the products: B2 H24 T4096 945 and 921 us)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x402, 6, 1);
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 1);
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 1);
+          }
+        } else __builtin_amdgcn_sched_barrier(0);
       }
     };
     if constexpr (AHEAD) {
@@ -358,18 +521,23 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
     l += other_half(l);
 
     // ---- the four waves meet at common shifts M (row) and C (column); a wave
-    // that had no tile has shifts of -inf, i.e. factors of zero
-    if (hl == 0) {
-      sm.m[wave][n] = m;
+    // that had no tile has shifts of -inf, i.e. factors of zero.  (The thread
+    // index anew: what the rest derives from it is not held through the tile
+    // loop.)
+    int et = tid;
+    asm volatile("" : "+v"(et));
+    const int en = et & 31, eh = (et >> 5) & 1;
+    if (eh == 0) {
+      sm.m[wave][en] = m;
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        sm.c[wave][cb * 32 + n] = cj[cb];
-        if (wave == 0) sm.bl[cb * 32 + n] = bl[cb];
+        sm.c[wave][cb * 32 + en] = cj[cb];
+        if (wave == 0) sm.bl[cb * 32 + en] = bl[cb];
       }
     }
     __syncthreads();
     // sm.f: each wave's column factors
-    for (int j = tid; j < D; j += kWaves * 64) {
+    for (int j = et; j < D; j += kWaves * 64) {
       float c[kWaves];
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) c[w] = sm.c[w][j];
@@ -377,79 +545,51 @@ __global__ __launch_bounds__(kWaves * 64, D <= 128 ? 2 : 1) void softmax_f32_ker
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) sm.f[w][j] = exp2_hw(c[w] - C);
     }
-    const float M = fmaxf(fmaxf(sm.m[0][n], sm.m[1][n]), fmaxf(sm.m[2][n], sm.m[3][n]));
+    const float M = fmaxf(fmaxf(sm.m[0][en], sm.m[1][en]), fmaxf(sm.m[2][en], sm.m[3][en]));
     const float fr = exp2_hw(m - M);
-    if (hl == 0) sm.l[wave][n] = l * fr;
+    if (eh == 0) sm.l[wave][en] = l * fr;
     __syncthreads();
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        const int j = cb * 32 + 8 * g + 4 * hl;
+        const int j = cb * 32 + 8 * g + 4 * eh;
         const f32x4 fc = *reinterpret_cast<const f32x4*>(&sm.f[wave][j]);
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          sm.o[wave][n * sm.OROW + j + u] = acc[cb][4 * g + u] * fr * fc[u];
+          sm.o[wave][en * sm.OROW + j + u] = acc[cb][4 * g + u] * fr * fc[u];
         __builtin_amdgcn_sched_barrier(0);
       }
     }
     __syncthreads();
-    // ---- epilogue, channel fastest: a thread keeps one channel (of each
-    // group of LPR) and takes every RPI-th row; the LDS reads of all its rows
+    // ---- epilogue, channel fastest; the LDS reads of all of a thread's rows
     // are independent
-    constexpr int LPR = D < 64 ? D : 64, RPI = kWaves * 64 / LPR;  // lanes a row, rows a pass
+    using Sh = Share<D>;
+    unsigned low = 0;  // outputs to recompute: bit group * kPasses + p
 #pragma unroll
-    for (int j0 = 0; j0 < D; j0 += LPR) {
-      const int j = j0 + tid % LPR;
+    for (int group = 0; group < Sh::kGroups; ++group) {
+      const int j = group * Sh::kLanes + et % Sh::kLanes;
       const bool on = j < d;
       const float C = fmaxf(fmaxf(sm.c[0][j], sm.c[1][j]), fmaxf(sm.c[2][j], sm.c[3][j]));
       const float ib = 1.f / sm.bl[j];
-      unsigned low = 0;  // bit p: this thread's row of pass p
+      unsigned lg = 0;
 #pragma unroll
-      for (int p = 0; p < kRows / RPI; ++p) {
-        const int r = p * RPI + tid / LPR, t = q0 + r;
+      for (int p = 0; p < Sh::kPasses; ++p) {
+        const int r = p * Sh::kStep + et / Sh::kLanes, t = q0 + r;
         const float L = (sm.l[0][r] + sm.l[1][r]) + (sm.l[2][r] + sm.l[3][r]);
         const int at = r * sm.OROW + j;
         const float mean = ((sm.o[0][at] + sm.o[1][at]) + (sm.o[2][at] + sm.o[3][at])) / L;
         const bool live = on && t < T;
         if (live) Oh[(size_t)t * d + j] = (log2_hw(mean) + C) * ib;
-        low |= live && !(mean >= kLow && mean <= kHigh) ? 1u << p : 0u;
+        lg |= live && !(mean >= kLow && mean <= kHigh) ? 1u << p : 0u;
       }
-      // rare: a mean that lost range (or is NaN), recomputed exactly, one row
-      // at a time by the whole wave
-      while (true) {
-        const uint64_t who = __ballot(low != 0);
-        if (who == 0) break;
-        const int src = __builtin_ctzll(who);
-        const int p = __builtin_ctz(__builtin_amdgcn_readlane(low, src));
-        const int r = p * RPI + (wave * 64 + src) / LPR;
-        // the row's flagged channels: lanes of the same row
-        const bool same = (tid / LPR) == (wave * 64 + src) / LPR && ((low >> p) & 1u);
-        uint64_t todo = __ballot(same);
-        if (same) low &= ~(1u << p);
-        while (todo != 0) {
-          int chs[kBatch];
-          float bls[kBatch];
-          int nb = 0, mych = 0;
-#pragma unroll
-          for (int c = 0; c < kBatch; ++c) {
-            chs[c] = 0;
-            bls[c] = 1.f;
-            if (todo == 0) continue;
-            const int ln = __builtin_ctzll(todo);
-            todo &= todo - 1;
-            chs[c] = j0 + (wave * 64 + ln) % LPR;
-            bls[c] = sm.bl[chs[c]];
-            nb = c + 1;
-            if (lane == c) mych = chs[c];
-          }
-          const float x = exact_row_f32(Qh, Kh, Vh, q0 + r, d, chs, bls, nb, scale2);
-          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // after the stores above
-          if (lane < nb) Oh[(size_t)(q0 + r) * d + mych] = x;
-        }
-      }
+      low |= lg << (group * Sh::kPasses);
     }
-    __syncthreads();  // the tables are read before the next block's
+    const bool redo = __any(low != 0);
+    if (lane == 0) sm.redo[wave] = redo;
+    __syncthreads();  // (also: the tables are read before the next block's)
+    if ((sm.redo[0] | sm.redo[1]) | (sm.redo[2] | sm.redo[3]))  // rare
+      recompute<D, FORM>(sm, rows, load4, Qh, Kh, Vh, Oh, T, d, qb, low, scale2);
   }
 }
 

@@ -83,8 +83,9 @@ def test_large_values(fem, T, d, size):
 
 @pytest.mark.parametrize("key", [0, 10, 70])
 @pytest.mark.parametrize("where", ["k", "v"])
-def test_nan_reaches_every_row_that_sees_it(fem, where, key):
-    q, k, v, b = inputs.draw(9750, 1, 1, 150, 64, dtype="f32", beta_lo=0.25, beta_hi=4.0)
+@pytest.mark.parametrize("d", [64, 20, 70])  # 20, 70: a key's row is read on into the next one's
+def test_nan_reaches_every_row_that_sees_it(fem, d, where, key):
+    q, k, v, b = inputs.draw(9750, 1, 1, 150, d, dtype="f32", beta_lo=0.25, beta_hi=4.0)
     want = ref(q, k, v, b)
     ch = slice(None) if where == "k" else slice(5, 6)
     (k if where == "k" else v)[0, 0, key, 5] = float("nan")
@@ -110,3 +111,13 @@ def test_infinite_and_lowest_values(fem):
     assert np.isposinf(got[0, 0, 20:, 1]).all()
     got[0, 0, 20:, 1] = want[0, 0, 20:, 1]
     assert np.abs(got - want).max() <= TOL
+
+
+@pytest.mark.parametrize("d", [32, 40, 64, 128, 200, 256])
+def test_some_outputs_recomputed(fem, d):
+    """A few columns of a long context whose maximum comes late: single
+    channels of single 32-row blocks, over several rounds of key tiles."""
+    q, k, v, b = inputs.draw(9770 + d, 1, 1, 330, d, dtype="f32", beta_lo=1.0, beta_hi=4.0)
+    v[0, 0, 31, 3] = v[0, 0, 150, 17] = v[0, 0, 329, d - 1] = 90.0
+    b[0, [3, 17, d - 1]] = 4.0
+    assert np.abs(read(fem, q, k, v, b) - ref(q, k, v, b)).max() <= TOL
