@@ -1183,33 +1183,51 @@ hipError_t launch(const void* Q, const void* K, const void* V, const float* beta
 // two a wave has half the products and half the softmax of a tile and the same
 // tilt, and an iteration takes ~0.7 of the time, so a workgroup's chain of
 // tiles shortens by that much and the whole work grows by 1.4.  That pays
-// where the chip is not full:
+// where the chip is not full (factors: time with one group over time with two):
 //   - T <= 128: one workgroup per (b, h) either way, half of whose waves would
-//     have no rows;
+//     have no rows: 1.02 to 1.2 at widths up to 64, 1.00 to 1.02 at 128, where
+//     T <= 64 (one tile) loses 2 to 4 % once the chip is full (300 heads, T64
+//     18.1 and 18.8 us), and always in the gated pass (128 heads, T64, both
+//     passes 19.2 and 19.8 us);
 //   - encoder read, up to 128 workgroups of 256 rows on the 256 compute units
-//     (twice as many still fit one each): B3 H6 T1571 d128/64 56.8 us with one
-//     group, 41.7 with two; at 256 workgroups (B4 H16 T1024 d64) 37.5 and 52.8;
+//     (twice as many still fit one each): 1.1 to 1.46 at every width and
+//     T = 256 .. 4096; B3 H6 T1571 d128/64 56.8 us with one group, 41.7 with
+//     two; at 256 workgroups (B4 H16 T1024 d64) 37.5 and 52.8;
 //   - causal read, up to 256 workgroups (one each, the longest of nqb row
 //     blocks sets the time) as long as the work of all of them, (nqb + 1) / (2
-//     nqb) of the longest each, stays ~0.8 of it: B4 H8 T1024 d64 (128
-//     workgroups) 34.3 and 28.2, B2 H16 T2048 d128 (256, nqb = 8) 85.3 and
-//     80.3, B4 H16 T1024 d128 (256, nqb = 4) 48.8 and 51.3; with 384
-//     workgroups the longest-first order balances one group (B3 H16 T2048
-//     d128 89.5 and 120).  The gated pass at d = 128 ends in a long epilogue
-//     that only the first group's waves run: B2 H16 T2048 108 and 120, so its
-//     bound is lower.
-inline bool split_keys(int B, int H, int T, bool causal, bool long_epilogue) {
-  if (T <= 128) return true;
+//     nqb) of the longest each, stays under a bound: kMostWork, twice that
+//     work in longest workgroups.  From nqb = 5 on 292 (at 288: 1.02 to 1.14).
+//     With fewer row blocks the shortest workgroup is no longer short, so the
+//     second one a compute unit gets shows: at nqb = 1 the 257th workgroup of
+//     128 rows (260: 0.82 at d128, 0.90 d64, 0.98 d64/32, 1.00 d32; at 256 1.13
+//     to 1.23), at nqb = 2 from ~210 (210: 1.09 and more; 228 0.92, 1.00), at
+//     nqb = 3 from ~250 (240: 1.04; 264: 0.98), at nqb = 4 from ~265 (265:
+//     1.00, 1.02; 280: 0.97, 0.99).  Narrow values, whose tilt is shorter,
+//     keep more (nqb = 2, 276: 1.05 at d32, 1.04 at d64/32; 291: 0.94).  The
+//     gated pass at d = 128 ends in a long epilogue that only the first
+//     group's waves run (both passes: nqb = 2 at 192 1.17, 198 0.96; nqb = 3 at
+//     192 1.14, 216 0.99; B2 H16 T2048 108 and 120 us), so its bounds are
+//     lower.
+template <int DK, int DV, int MODE>
+inline bool split_keys(int B, int H, int T, bool causal) {
   const size_t nqb = ((size_t)T + 255) / 256, wgs = nqb * B * H;
+  constexpr bool kMixes = MODE == kGated && DV == 128;  // the long epilogue
+  if (T <= 128) return DV < 128 || T > 64 || (wgs <= 256 && !kMixes);
   if (!causal) return wgs <= 128;
-  return wgs <= 256 && wgs * (nqb + 1) <= (long_epilogue ? 230 : 292) * nqb;
+  constexpr int kMostWork[4][5] = {  // nqb = 1, 2, 3, 4, 5 and more
+      {292, 288, 276, 292, 292},     // d = 32
+      {256, 276, 276, 292, 292},     // d = 64, 32
+      {256, 210, 250, 265, 292},     // wider values
+      {230, 192, 200, 230, 230}};    // the gated pass at d = 128
+  constexpr int kRow = DK == 32 ? 0 : DV == 32 ? 1 : kMixes ? 3 : 2;
+  return wgs <= 256 && wgs * (nqb + 1) <= (size_t)kMostWork[kRow][nqb < 5 ? nqb - 1 : 4] * nqb;
 }
 
 template <int DK, int DV, int MODE, bool CAUSAL, bool OBF16>
 hipError_t launch_kg(const void* Q, const void* K, const void* V, const float* beta,
                      const float* lam, const float* gate, void* out, int B, int H, int T,
                      hipStream_t stream, float* lse = nullptr) {
-  if (split_keys(B, H, T, CAUSAL, MODE == kGated && DV == 128))
+  if (split_keys<DK, DV, MODE>(B, H, T, CAUSAL))
     return launch<Cfg<DK, DV, 8, MODE, CAUSAL, OBF16, 2>>(Q, K, V, beta, lam, gate, out, B, H, T,
                                                           stream, lse);
   return launch<Cfg<DK, DV, 8, MODE, CAUSAL, OBF16, 1>>(Q, K, V, beta, lam, gate, out, B, H, T,

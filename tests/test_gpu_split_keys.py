@@ -62,3 +62,24 @@ def test_repair_and_lse_with_two_groups(fem):
     s = torch.matmul(q.double(), k.double().transpose(2, 3)) / 8.0
     s = s.masked_fill(torch.ones(200, 200, dtype=torch.bool).triu(1), -np.inf)
     assert (lse.cpu().double() - torch.logsumexp(s, -1)).abs().max().item() <= 1e-2
+
+
+# Which kernel a launch takes, from the bits: the same heads in a launch of many
+# (one key group) are equal where the smaller one takes one group too, and
+# differ (P is rounded at other shifts) where it takes two.
+@pytest.mark.parametrize("dk,dv,T,heads,two", [
+    (64, 64, 256, 128, True), (64, 64, 256, 146, False), (128, 128, 200, 140, False),
+    (64, 32, 256, 140, False), (32, 32, 256, 146, True), (128, 128, 500, 70, True),
+    (128, 128, 400, 76, False), (64, 64, 512, 92, False), (32, 32, 500, 96, True),
+    (32, 32, 500, 98, False), (128, 64, 768, 60, True), (64, 64, 768, 66, False),
+    (128, 128, 1000, 52, True), (128, 128, 1000, 56, False), (128, 128, 2048, 32, True),
+    (128, 128, 60, 128, True), (128, 128, 60, 300, False),
+])
+def test_rule(fem, dk, dv, T, heads, two):
+    many = 2 * (max(300, heads) if T <= 256 else 160)
+    q, k, v, b = (t.cuda() for t in inputs.draw(8500 + T + dk + dv, many // 2, 2, T, dk, dv,
+                                                beta_lo=0.1, beta_hi=8.0))
+    ref = fem.fem_softmax_fwd_ex(q, k, v, b)[: heads // 2]
+    got = fem.fem_softmax_fwd_ex(*(t[: heads // 2].contiguous() for t in (q, k, v)), b)
+    torch.cuda.synchronize()
+    assert torch.equal(ref, got) != two
