@@ -872,14 +872,12 @@ __device__ __forceinline__ void scan_chunk(ScanSmem<PRIOR, CH, NSUB>& sm, f32x16
 // per state entry: S[j][*] carries row shift c_j, z needs none, c is the max.
 // GLA: the state entering segment s+1 is the one entering s, decayed by the
 // total log-decay of segment s along its key channel, plus the own state of s.
-// Latency bounds it.  Up to kPrefixFew segments take one batch of PB = 8 and
-// the linear prior goes on in batches of 8 up to kPrefixOne (PB = 32 gained it
-// nothing: B5 H8 T3000, 12 segments, 45.3 and 45.6 us a call); GLA, whose
-// decays lengthen the chain between batches, takes one batch of 32 (20 segments
-// of 24 (b, h): 11.7 us in batches of 8, 8.1 so, 32 in prefix_wide_kernel, most
-// of whose groups would be idle).  prefix_wide_kernel takes more.
-constexpr int kPrefixFew = 9, kPrefixOne = 33;
-template <int PRIOR, int PB>
+// Latency bounds it: the loads of kPrefixBatch segments are issued before their
+// (sequential) combination.  Batches of 32 gained neither prior anything (us a
+// call, 8 and 32: 24 (b, h) of T8192, 19 segments, linear 58.6 and 58.5, GLA 88.9
+// and 89.3; 12 of T8192, 32 segments, 43.7 and 43.5, 60.6 and 60.4).
+constexpr int kPrefixBatch = 8;
+template <int PRIOR>
 __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ own,
                                                      float* __restrict__ pre, int nseg) {
   constexpr int SF = state_floats<PRIOR>();
@@ -891,8 +889,7 @@ __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ o
   const int j = e < DV * DK ? e / DK : (e >= DV * DK + DK ? e - DV * DK - DK : -1);
   // key channel of an S or z entry (decay), -1 for a shift entry
   const int kc = e < DV * DK ? e % DK : (e < DV * DK + DK ? e - DV * DK : -1);
-  // segments in batches of PB: every load of a batch is issued before the
-  // batch's (sequential) combination
+  constexpr int PB = kPrefixBatch;
   float acc = 0.f, C = -INFINITY;
   for (int s0 = 0; s0 + 1 < nseg; s0 += PB) {
     float val[PB], cs[PB], lg[PB];
@@ -1343,6 +1340,25 @@ struct ScanPlan {
   }
 };
 
+// The prefix's segments over thread groups (prefix_wide_kernel), or walked in
+// batches?  The groups save a latency per batch but take 7.8 times the
+// workgroups and combine every segment twice, so they need many segments, and
+// more of them the more (b, h) there are and with decays (us a call, batches and
+// groups, where they are about even; at 1 (b, h) of T32768, 512 segments, 118
+// and 49, GLA 127 and 63):
+//   linear: 1 to 8 (b, h) 34 segments 20.5 and 19.6 .. 27.5 and 27.2, 9 28.0 and
+//     28.1; 25 segments 18.7 and 19.5 .. 21.2 and 22.9; 11, 43 segments, 42.4 and
+//     41.7; 12 32.9 and 33.0 at 42, 67.2 and 67.8 at 40; 15, 34 segments, 31.3 and
+//     35.7;
+//   GLA: 51 segments, 1 (b, h) 25.7 and 24.5, 6 32.8 and 32.7, 8 33.6 and 34.9;
+//     7 at 57 35.0 and 34.2; 8 at 57 34.9 and 35.1, at 64 36.6 and 35.1; 10, 51
+//     segments, 33.8 and 41.7; 15, 34 segments, 30.6 and 43.1.
+template <int PRIOR>
+bool prefix_splits(int nbh, int nseg) {
+  if (PRIOR == kGla) return nseg > 48 + nbh;
+  return nseg > 33 && (nbh <= 9 || nseg >= 43);
+}
+
 template <int PRIOR, int CH, int NSUB>
 hipError_t launch_scan(const void* Q, const void* K, const void* V, const float* G,
                        const float* beta, float* out, int B, int H, int T, void* wsv,
@@ -1367,12 +1383,8 @@ hipError_t launch_scan(const void* Q, const void* K, const void* V, const float*
     if (e == hipSuccess) {
       float* pre = ws + (size_t)nbh * nseg * SF;
       const dim3 pgrid((unsigned)((STATE + NTH - 1) / NTH), (unsigned)nbh);
-      if (nseg <= (PRIOR == kGla ? kPrefixFew : kPrefixOne))
-        hipLaunchKernelGGL((prefix_kernel<PRIOR, kPrefixFew - 1>), pgrid, dim3(NTH), 0, stream, ws,
-                           pre, nseg);
-      else if (nseg <= kPrefixOne)
-        hipLaunchKernelGGL((prefix_kernel<PRIOR, kPrefixOne - 1>), pgrid, dim3(NTH), 0, stream, ws,
-                           pre, nseg);
+      if (!prefix_splits<PRIOR>(nbh, nseg))
+        hipLaunchKernelGGL(prefix_kernel<PRIOR>, pgrid, dim3(NTH), 0, stream, ws, pre, nseg);
       else
         hipLaunchKernelGGL(prefix_wide_kernel<PRIOR>, dim3((unsigned)(STATE / PEN), (unsigned)nbh),
                            dim3(NTH), 0, stream, ws, pre, nseg);

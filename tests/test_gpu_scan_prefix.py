@@ -49,3 +49,14 @@ def test_segment_counts(fem, B, H, T, chunk, nseg, gla):
         want = oracle.fem_linear_recurrent(*n, bn)
     torch.cuda.synchronize()
     assert np.abs(out[:, heads].cpu().double().numpy() - want).max() <= TOL
+
+
+# Both sides of the rule that splits the segments over thread groups: linear
+# above 33 segments up to 9 (b, h) and from 43 at 10 and 11; GLA above 48 + B H.
+@pytest.mark.parametrize("B,H,T,nseg", [
+    (1, 9, 2112, 33), (1, 9, 2176, 34), (2, 5, 2688, 42), (1, 11, 2752, 43), (1, 12, 2688, 42),
+    (1, 1, 3136, 49), (1, 1, 3200, 50), (2, 4, 3584, 56), (1, 8, 3640, 57), (1, 9, 3584, 56),
+])
+@pytest.mark.parametrize("gla", [False, True])
+def test_split_rule(fem, B, H, T, nseg, gla):
+    test_segment_counts(fem, B, H, T, 64, nseg, gla)
