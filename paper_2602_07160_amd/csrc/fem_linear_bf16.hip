@@ -876,8 +876,14 @@ __device__ __forceinline__ void scan_chunk(ScanSmem<PRIOR, CH, NSUB>& sm, f32x16
 // (sequential) combination.  Batches of 32 gained neither prior anything (us a
 // call, 8 and 32: 24 (b, h) of T8192, 19 segments, linear 58.6 and 58.5, GLA 88.9
 // and 89.3; 12 of T8192, 32 segments, 43.7 and 43.5, 60.6 and 60.4).
-constexpr int kPrefixBatch = 8;
-template <int PRIOR>
+// Loads past the last segment are skipped (SKIP) or repeat it.  Without decays
+// the branches cost more than the loads they save, except in a first and only
+// batch of few (us a call, skipped and repeated: 16 (b, h) of T2048, 32
+// segments, 30.8 and 30.0; 1 of T520, 9, 15.4 and 15.1; 100 of T320, 5, 25.8
+// and 26.0; 170 of T192, 3, 24.9 and 25.6); with them every batch ends in fewer
+// exponentials (GLA, 15 of T2176 30.5 and 37.7).
+constexpr int kPrefixBatch = 8, kPrefixSkip = 6;
+template <int PRIOR, bool SKIP>
 __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ own,
                                                      float* __restrict__ pre, int nseg) {
   constexpr int SF = state_floats<PRIOR>();
@@ -896,8 +902,8 @@ __global__ __launch_bounds__(NTH) void prefix_kernel(const float* __restrict__ o
 #pragma unroll
     for (int u = 0; u < PB; ++u) {
       val[u] = cs[u] = lg[u] = 0.f;
-      if (s0 + u + 1 >= nseg) continue;  // the same for every thread
-      const size_t o = (size_t)(s0 + u) * SF;
+      if (SKIP && s0 + u + 1 >= nseg) continue;  // the same for every thread
+      const size_t o = (size_t)min(s0 + u, nseg - 2) * SF;
       val[u] = ob[o + e];
       cs[u] = j >= 0 ? ob[o + DV * DK + DK + j] : 0.f;
       lg[u] = (PRIOR == kGla && kc >= 0) ? ob[o + STATE + kc] : 0.f;
@@ -1344,19 +1350,19 @@ struct ScanPlan {
 // batches?  The groups save a latency per batch but take 7.8 times the
 // workgroups and combine every segment twice, so they need many segments, and
 // more of them the more (b, h) there are and with decays (us a call, batches and
-// groups, where they are about even; at 1 (b, h) of T32768, 512 segments, 118
-// and 49, GLA 127 and 63):
-//   linear: 1 to 8 (b, h) 34 segments 20.5 and 19.6 .. 27.5 and 27.2, 9 28.0 and
-//     28.1; 25 segments 18.7 and 19.5 .. 21.2 and 22.9; 11, 43 segments, 42.4 and
-//     41.7; 12 32.9 and 33.0 at 42, 67.2 and 67.8 at 40; 15, 34 segments, 31.3 and
-//     35.7;
-//   GLA: 51 segments, 1 (b, h) 25.7 and 24.5, 6 32.8 and 32.7, 8 33.6 and 34.9;
-//     7 at 57 35.0 and 34.2; 8 at 57 34.9 and 35.1, at 64 36.6 and 35.1; 10, 51
-//     segments, 33.8 and 41.7; 15, 34 segments, 30.6 and 43.1.
+// groups, where they are about even; at 1 (b, h) of T32768, 512 segments, 104
+// and 48, GLA 127 and 63):
+//   linear: 34 segments of 1 (b, h) 19.6 and 19.3, of 4 21.2 and 21.0, of 6 22.4
+//     and 22.4, of 8 26.6 and 27.3; 29 of 1 18.7 and 19.4; 42 of 8 29.1 and
+//     28.6, of 9 29.9 and 29.5, of 10 30.5 and 30.8; of 10 at 51 32.8 and 32.5,
+//     of 11 at 46 32.1 and 32.7; 34 of 15 30.6 and 35.7;
+//   GLA: 51 segments of 1 (b, h) 25.7 and 24.5, of 6 32.8 and 32.7, of 8 33.6
+//     and 34.9, of 10 33.8 and 41.7; 57 of 7 35.0 and 34.2, of 8 34.9 and 35.1;
+//     64 of 8 36.6 and 35.1; 34 of 15 30.6 and 43.1.
 template <int PRIOR>
 bool prefix_splits(int nbh, int nseg) {
   if (PRIOR == kGla) return nseg > 48 + nbh;
-  return nseg > 33 && (nbh <= 9 || nseg >= 43);
+  return nbh < 10 && nseg > max(33, 29 + nbh);
 }
 
 template <int PRIOR, int CH, int NSUB>
@@ -1383,11 +1389,15 @@ hipError_t launch_scan(const void* Q, const void* K, const void* V, const float*
     if (e == hipSuccess) {
       float* pre = ws + (size_t)nbh * nseg * SF;
       const dim3 pgrid((unsigned)((STATE + NTH - 1) / NTH), (unsigned)nbh);
-      if (!prefix_splits<PRIOR>(nbh, nseg))
-        hipLaunchKernelGGL(prefix_kernel<PRIOR>, pgrid, dim3(NTH), 0, stream, ws, pre, nseg);
-      else
+      if (prefix_splits<PRIOR>(nbh, nseg))
         hipLaunchKernelGGL(prefix_wide_kernel<PRIOR>, dim3((unsigned)(STATE / PEN), (unsigned)nbh),
                            dim3(NTH), 0, stream, ws, pre, nseg);
+      else if (PRIOR == kGla || nseg <= kPrefixSkip)
+        hipLaunchKernelGGL((prefix_kernel<PRIOR, true>), pgrid, dim3(NTH), 0, stream, ws, pre,
+                           nseg);
+      else if constexpr (PRIOR == kElu)
+        hipLaunchKernelGGL((prefix_kernel<PRIOR, false>), pgrid, dim3(NTH), 0, stream, ws, pre,
+                           nseg);
       e = hipGetLastError();
     }
   }

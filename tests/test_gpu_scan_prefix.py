@@ -51,11 +51,13 @@ def test_segment_counts(fem, B, H, T, chunk, nseg, gla):
     assert np.abs(out[:, heads].cpu().double().numpy() - want).max() <= TOL
 
 
-# Both sides of the rule that splits the segments over thread groups: linear
-# above 33 segments up to 9 (b, h) and from 43 at 10 and 11; GLA above 48 + B H.
+# Both sides of the rules: linear from 34 segments up to 4 (b, h), above 29 + B H
+# up to 9; GLA above 48 + B H; the linear prior's batches skip loads up to 6
+# segments and repeat the last one's from 7 on.
 @pytest.mark.parametrize("B,H,T,nseg", [
-    (1, 9, 2112, 33), (1, 9, 2176, 34), (2, 5, 2688, 42), (1, 11, 2752, 43), (1, 12, 2688, 42),
-    (1, 1, 3136, 49), (1, 1, 3200, 50), (2, 4, 3584, 56), (1, 8, 3640, 57), (1, 9, 3584, 56),
+    (1, 85, 384, 6), (1, 73, 440, 7), (1, 4, 2112, 33), (1, 4, 2176, 34), (1, 9, 2432, 38),
+    (1, 9, 2496, 39), (2, 5, 3264, 51), (1, 1, 3136, 49), (1, 1, 3200, 50), (2, 4, 3584, 56),
+    (1, 8, 3640, 57), (1, 9, 3584, 56),
 ])
 @pytest.mark.parametrize("gla", [False, True])
 def test_split_rule(fem, B, H, T, nseg, gla):
