@@ -593,6 +593,103 @@ __global__ __launch_bounds__(kWaves * 64, D <= 32 ? 3 : D <= 128 ? 2 : 1) void s
   }
 }
 
+// Short contexts: one workgroup per query row, since a 32 x 32 tile then holds
+// few live entries and one wave walks its whole chain of products (see
+// takes_rows).  Sixteen lanes form a score (a row of K in 64-byte segments); then
+// a thread has one channel and every so manieth eight of the row's keys, and the
+// key groups meet in LDS.  With m the row's largest score and M the largest
+// fma(beta v, s - m) so far a term is 2^((beta v - M) + (s - m)), both parts near
+// zero where the term counts; where M is so large that its own rounding matters
+// it is 2^(x - M) with x rounded like M.  Bound by latency: T1, T16 and T64 of one
+// (b, h) at d256 5.2, 5.7 and 8.9 us a call (19.3, 22.5 and 26.1 in tiles), at d130
+// 4.9, 5.3 and 7.8 (26.0, 29.9 and 36.0).  Error against float64 2e-8 to 1e-7.
+constexpr int kRowKeys = 512;  // longest context
+constexpr int kScoreLanes = 16;
+
+template <int NT>
+__global__ __launch_bounds__(NT) void softmax_f32_rows_kernel(
+    const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+    const float* __restrict__ beta, float* __restrict__ out, int H, int T, int d, int lanes_log2) {
+  constexpr int NU = kMaxD / kScoreLanes, KU = 8;
+  constexpr float kBig = 0x1p20f;
+  __shared__ float sc[kRowKeys + KU];
+  __shared__ float pm[NT], ps[NT];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int bh = blockIdx.x, h = bh % H, t = T - 1 - (int)blockIdx.y, n = t + 1;
+  const size_t base = (size_t)bh * T * d;
+  const float* Kh = K + base;
+  const int j = tid & ((1 << lanes_log2) - 1), grp = tid >> lanes_log2, ngrp = NT >> lanes_log2;
+  const float* vj = V + base + min(j, d - 1);
+  const float bl = beta[h * d + min(j, d - 1)] * kLog2e;
+  const auto load_v = [&](int i0, float (&v)[KU]) {  // (0 past the row: its score is -inf)
+#pragma unroll
+    for (int u = 0; u < KU; ++u) v[u] = i0 + u < n ? vj[(size_t)(i0 + u) * d] : 0.f;
+  };
+  float v[KU];
+  load_v(grp * KU, v);
+  {
+    const int c0 = tid % kScoreLanes;
+    float qr[NU];
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      qr[u] = c0 + u * kScoreLanes < d ? Q[base + (size_t)t * d + c0 + u * kScoreLanes] : 0.f;
+    const float scale2 = kLog2e / sqrtf((float)d);
+    for (int i = tid / kScoreLanes; i < n; i += NT / kScoreLanes) {
+      float dot = 0.f;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int c = c0 + u * kScoreLanes;
+        if (u * kScoreLanes < d) dot = fmaf(qr[u], c < d ? Kh[(size_t)i * d + c] : 0.f, dot);
+      }
+#pragma unroll
+      for (int x = kScoreLanes / 2; x > 0; x >>= 1) dot += __shfl_xor(dot, x);
+      if (c0 == 0) sc[i] = dot * scale2;
+    }
+  }
+  if (tid < KU) sc[n + tid] = -INFINITY;
+  __syncthreads();
+  // the prior's normaliser, by every wave
+  float m = -INFINITY, l = 0.f;
+  for (int i = lane; i < n; i += 64) m = fmaxf(m, sc[i]);
+  m = finite(wave_max(m));
+  for (int i = lane; i < n; i += 64) l += exp2_hw(sc[i] - m);
+  l = wave_sum(l);
+  float M = -INFINITY, S = 0.f;
+  for (int i0 = grp * KU; i0 < n; i0 += ngrp * KU) {
+    float vn[KU], st[KU], x[KU];
+    load_v(i0 + ngrp * KU, vn);
+    float mx = M;
+#pragma unroll
+    for (int u = 0; u < KU; ++u) {
+      st[u] = sc[i0 + u] - m;
+      x[u] = fmaf(v[u], bl, st[u]);
+      mx = fmaxf(mx, x[u]);
+    }
+    const float at = finite(mx);
+    const bool big = fabsf(at) >= kBig;
+    float e = 0.f;
+#pragma unroll
+    for (int u = 0; u < KU; ++u)
+      e += exp2_hw(big ? x[u] - at : fmaf(v[u], bl, -at) + st[u]);
+    S = fmaf(S, exp2_hw(M - at), e);
+    M = mx;
+#pragma unroll
+    for (int u = 0; u < KU; ++u) v[u] = vn[u];
+  }
+  pm[tid] = M;
+  ps[tid] = S;
+  __syncthreads();
+  if (grp == 0 && j < d) {
+    const int live = min(ngrp, (n + KU - 1) / KU);  // groups that had keys
+    for (int g = 1; g < live; ++g) M = fmaxf(M, pm[(g << lanes_log2) + j]);
+    const float at = finite(M);
+    S = 0.f;
+    for (int g = 0; g < live; ++g)
+      S = fmaf(ps[(g << lanes_log2) + j], exp2_hw(pm[(g << lanes_log2) + j] - at), S);
+    out[base + (size_t)t * d + j] = (M + (log2_hw(S) - log2_hw(l))) / bl;
+  }
+}
+
 template <int D, int FORM>
 hipError_t launch(const float* Q, const float* K, const float* V, const float* beta, float* out,
                   int nbh, int H, int T, int d, hipStream_t stream) {
@@ -603,6 +700,61 @@ hipError_t launch(const float* Q, const float* K, const float* V, const float* b
   return hipGetLastError();
 }
 
+// One workgroup per row, or per 32 rows?  By the rows (nbh T), the work (nbh T T)
+// and T.  Measured (us a call, rows and tiles; 1, 8, 32 and 128 (b, h)) at:
+//   d = 7: 8 of T48 6.4 and 6.7, 32 of T32 7.1 and 6.9, 200 of T8 5.0 and 6.4,
+//     256 of T16 8.4 and 6.6;
+//   d = 32: 1 of T32 5.4 and 5.6, 32 5.5 and 6.0, 32 of T48 6.8 and 5.8, 200 of
+//     T8 5.0 and 6.1, 128 of T16 8.1 and 5.5;
+//   d = 50: 8 of T128 10.7 and 12.2, 32 of T64 10.8 and 11.8, of T96 15.9 and
+//     12.0, 128 of T16 8.4 and 10.1, of T32 14.2 and 11.9;
+//   d = 64: 1 of T192 9.6 and 10.5, of T256 11.4 and 10.5, 8 of T96 7.5 and 8.4,
+//     of T128 10.8 and 8.5, 32 of T48 7.8 and 8.4, 128 of T8 5.2 and 7.0, of T16
+//     8.3 and 7.6;
+//   d = 100: 8 of T128 14.7 and 15.1, 32 of T64 13.4 and 15.3, of T96 21.1 and
+//     15.2, 128 of T16 9.3 and 13.3, of T32 17.2 and 15.3;
+//   d = 128: 1 of T256 16.3 and 17.7, 8 of T96 9.1 and 13.2, of T128 15.1 and
+//     13.1, 32 of T48 8.3 and 13.0, of T64 13.5 and 13.1, 128 of T16 9.2 and 11.2;
+//   d = 130: 1 of T512 40 and 79, 32 of T96 29 and 37, of T128 47 and 39, 128 of
+//     T48 36 and 37; d = 200: 32 of T96 33 and 36, 128 of T48 40 and 41;
+//   d = 256: 1 of T256 26 and 37, 8 of T128 21 and 27, 32 of T64 20 and 27, of T96
+//     34 and 27, 128 of T32 24 and 27, of T48 42 and 27.
+bool takes_rows(int nbh, int T, int d) {
+  struct Most {
+    int rows, work, T;
+  };
+  constexpr Most kMost[4][2] = {{{2048, 32768, 32}, {2048, 18432, 48}},       // d = 32; narrower
+                                {{1536, 73728, 192}, {2048, 131072, 512}},   // d = 64; 33 .. 63
+                                {{2048, 73728, 256}, {2048, 131072, 512}},   // d = 128; 65 .. 127
+                                {{4096, 131072, 512}, {6144, 294912, 512}}}; // d = 256; 129 .. 255
+  const int w = d <= 32 ? 0 : d <= 64 ? 1 : d <= 128 ? 2 : 3;
+  const Most m = kMost[w][d == 32 << w ? 0 : 1];
+  return T <= m.T && (int64_t)nbh * T <= m.rows && (int64_t)nbh * T * T <= m.work;
+}
+
+template <int NT>
+hipError_t launch_rows(const float* Q, const float* K, const float* V, const float* beta, float* out,
+                       int nbh, int H, int T, int d, int lanes_log2, hipStream_t stream) {
+  hipLaunchKernelGGL(softmax_f32_rows_kernel<NT>, dim3((unsigned)nbh, (unsigned)T), dim3(NT), 0,
+                     stream, Q, K, V, beta, out, H, T, d, lanes_log2);
+  return hipGetLastError();
+}
+
+// As many threads as have keys (eight each) or form the scores in two rounds, up
+// to 256; 512 where the rows leave most of the chip idle: 8 (b, h) of T96 d64 7.5
+// us a call and 9.2 with 256, of T128 11.6 and 10.8.
+hipError_t launch_rows(const float* Q, const float* K, const float* V, const float* beta, float* out,
+                       int nbh, int H, int T, int d, hipStream_t stream) {
+  int lanes_log2 = 3;  // a power of two of lanes covers the channels
+  while ((1 << lanes_log2) < d) ++lanes_log2;
+  const int threads = max((T + 7) / 8 << lanes_log2, 8 * T);
+  const auto go = [&](auto f) { return f(Q, K, V, beta, out, nbh, H, T, d, lanes_log2, stream); };
+  if (threads <= 64) return go(launch_rows<64>);
+  if (threads <= 128) return go(launch_rows<128>);
+  if (d <= 32 || threads <= 256 || nbh * T > 768) return go(launch_rows<256>);
+  return go(launch_rows<512>);
+}
+
 }  // namespace
 
 hipError_t launch_softmax_f32(const float* Q, const float* K, const float* V, const float* beta,
@@ -610,6 +762,7 @@ hipError_t launch_softmax_f32(const float* Q, const float* K, const float* V, co
   if (d < 1 || d > kMaxD) return hipErrorInvalidValue;
   const int D = d <= 32 ? 32 : d <= 64 ? 64 : d <= 128 ? 128 : 256;
   const int form = d == D ? kFull : d % 4 == 0 ? kVec4 : kAny;
+  if (takes_rows(B * H, T, d)) return launch_rows(Q, K, V, beta, out, B * H, H, T, d, stream);
   const auto go = [&](auto f) { return f(Q, K, V, beta, out, B * H, H, T, d, stream); };
 #define FEM_F32_FORM(W)                                  \
   if (D == W) {                                          \
