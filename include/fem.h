@@ -84,9 +84,16 @@ typedef enum {
  *   beta    : [H, d] float32, > 0
  *   out     : [B, H, T, d] float32
  *   d       : 32, 64 or 128 for FEM_DTYPE_BF16 (matrix-core path);
- *             any 1 <= d <= 256 for FEM_DTYPE_F32 (fp32 matrix path)
+ *             any 1 <= d <= 256 for FEM_DTYPE_F32 (fp32 path)
  *
  * Score scale is fixed at 1/sqrt(d).  Returns a fem_status.
+ *
+ * The kernel is chosen by B * H, T and the widths, and kernels round at
+ * different places: the same head may differ at rounding level between calls of
+ * different B * H (bf16 inputs: 2^-9 of a probability and up to 2^-8 / beta of a
+ * value's exponential for beta >= 0.5, less below; fp32 inputs: about 1e-6), and
+ * so may this read and that of fem_softmax_gated_fwd at lam = g = 1.  Calls of
+ * the same sizes give the same bits.
  */
 int fem_softmax_fwd(const void* Q, const void* K, const void* V,
                     const float* beta, float* out,

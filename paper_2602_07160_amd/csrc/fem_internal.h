@@ -65,7 +65,8 @@ hipError_t launch_decode_noalloc_bf16(const void* q, const void* Kc, const void*
                                       const int* lens, const float* beta, float* out, int B,
                                       int H, int L, int dk, int dv, hipStream_t stream);
 
-// fp32 softmax-prior read on the fp32 matrix instructions (short contexts: a workgroup per row), 1 <= d <= 256.
+// fp32 softmax-prior read on the fp32 matrix instructions, or a workgroup per row
+// (short contexts), 1 <= d <= 256.
 hipError_t launch_softmax_f32(const float* Q, const float* K, const float* V,
                               const float* beta, float* out,
                               int B, int H, int T, int d, hipStream_t stream);
