@@ -141,8 +141,9 @@ __device__ __forceinline__ void lse_add(float& M, float& S, const float (&x)[N])
 // taking one row and eight channels at a time, which formed the row's scores
 // anew for each; then the first kernel, one workgroup a row): B4 H12 T1024 d64
 // 213, 3085 and 3980; B2 H12 T1024 d128 384, 9370 and 2440; B1 H12 T1024 d256
-// 714, 32100 and 1580.  Only where four blocks a head leave the chip idle is
-// the first one ahead: B1 H2 T128 d64 36, 600 and 32, d256 120, 4660 and 37.
+// 714, 32100 and 1580.  The first one is ahead (by up to 1.9) where few blocks
+// leave the chip idle: B1 H16 T96 d100 52, 2200 and 29, B1 H8 T256 d128 100, 2670
+// and 88, B1 H1 T1024 d128 343, 9330 and 243.
 template <int D, int FORM, class Rows, class Load4>
 __device__ __forceinline__ void recompute(F32Smem<D>& sm, Rows&& rows, Load4&& load4,
                                           const float* __restrict__ Qh,
